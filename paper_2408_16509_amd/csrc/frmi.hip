@@ -909,7 +909,7 @@ void tet_smin(fr_ctx c, DevBlock& b, const double* uprev) {
   const int g = (int)((b.n + 255) / 256);
   unsigned long long* sown = (unsigned long long*)b.sown;
   int pk = c->prof_begin("filter_smin");
-  tet_sown<<<g, 256, 0, c->stream>>>(uprev + b.native_off, sown, b.E, b.n, c->prm.gamma);
+  tet_sown<<<(unsigned)(b.E / 64), TF_NT, 0, c->stream>>>(uprev + b.native_off, sown, b.E, b.n, c->prm.gamma);
   elem_smin<<<g, 256, 0, c->stream>>>(sown, b.nbr_elem, b.nfaces, b.smin, b.E, b.n);
   c->prof_end(pk);
 }
@@ -920,16 +920,16 @@ void tet_candidates(fr_ctx c, DevBlock& b, const double* u, const StageFuse* fz 
   const int nb = (int)((b.n + 255) / 256);
   int pk = c->prof_begin(fz ? "rk4_stage_filter_detect_tet" : "filter_detect");
   k_filter_reset<<<grid_for(b.n, 256), 256, 0, c->stream>>>(b.f_det, c->f_k + o, c->f_evals + o, b.n);
-  const unsigned gE = (unsigned)((b.E + 255) / 256);
+  const unsigned gE = (unsigned)(b.E / 64);
   if (!fz)
-    tet_filter_detect<PlainSrc><<<nb, 256, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E, b.n, F, b.f_det,
+    tet_filter_detect<PlainSrc><<<gE, TF_NT, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E, b.n, F, b.f_det,
                                                            nullptr);
   else if (fz->k32)
-    tet_filter_detect<RkStageSrc<float>><<<gE, 256, 0, c->stream>>>(
+    tet_filter_detect<RkStageSrc<float>><<<gE, TF_NT, 0, c->stream>>>(
         stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, F, b.f_det,
         fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   else
-    tet_filter_detect<RkStageSrc<double>><<<gE, 256, 0, c->stream>>>(
+    tet_filter_detect<RkStageSrc<double>><<<gE, TF_NT, 0, c->stream>>>(
         stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, F, b.f_det,
         fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   k_flag_count<<<nb, 256, 0, c->stream>>>(b.f_det, b.n, b.f_cnt);
