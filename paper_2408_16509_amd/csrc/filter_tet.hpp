@@ -187,13 +187,12 @@ __global__ void __launch_bounds__(TF_NT) tet_sown(const double* __restrict__ u, 
   sown[e] = ord_bits(smin);
 }
 
-// Detection: pessimistic test at every solution point, as the hexahedral detection (flag
-// must be cleared before).  With an RK stage source the pass also performs the stage
+// Detection: pessimistic test at every solution point, as the hexahedral detection.  With an RK stage source the pass also performs the stage
 // update (all E_pad elements), and cand64 (if not null) receives the FP64 stage state of
 // the flagged elements.
 template <typename Src>
 __global__ void __launch_bounds__(TF_NT) tet_filter_detect(Src src, const double* __restrict__ smin_a, int64_t E,
-                                                           int64_t n, FiltPrm F, int32_t* __restrict__ flag,
+                                                           int64_t n, FiltPrm F, CandList L,
                                                            double* __restrict__ cand64) {
   __shared__ int BAD[64];
   constexpr bool kUpdate = !std::is_same<Src, PlainSrc>::value;
@@ -206,14 +205,15 @@ __global__ void __launch_bounds__(TF_NT) tet_filter_detect(Src src, const double
   const double lsb = sbm > 0 ? log(sbm) : -INFINITY;
   bool bad = false;
   tet_tile_points(src, E, e, g, [&](const double w[5]) { bad = bad || maybe_violates(w, lsb, F); });
-  bad = bad && e < n;
-  if (bad) flag[e] = 1;
+  __syncthreads();
+  if (bad && e < n) BAD[lane] = 1;
+  __syncthreads();
+  if (g == 0) {
+    L.reset(e);
+    L.append(BAD[lane] != 0, e);
+  }
   if constexpr (kUpdate) {
-    if (cand64 == nullptr) return;
-    __syncthreads();
-    if (bad) BAD[lane] = 1;
-    __syncthreads();
-    if (!BAD[lane]) return;
+    if (cand64 == nullptr || !BAD[lane]) return;
     for (int i = 0; i < TF_ZG * 5; ++i) {
       const int64_t j = ((int64_t)(g * TF_ZG) * 5 + i) * E + e;
       cand64[j] = src.stage(j);

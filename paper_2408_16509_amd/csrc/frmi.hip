@@ -59,9 +59,9 @@ struct DevBlock {
   int32_t* cpos = nullptr;  // native index -> canonical index within the block [E] (-1: padding)
   double* sown = nullptr;   // entropy filter: own min entropy [E]
   double* smin = nullptr;   // entropy filter: neighbourhood min entropy [E]
-  int32_t* f_det = nullptr;   // entropy filter: detection flags [n]
+  int32_t* f_det = nullptr;   // entropy filter: slot + 1 of the last call that listed the element [n]
   int32_t* f_list = nullptr;  // candidates of the search, native ids [n]
-  int32_t* f_cnt = nullptr;   // per-256 offsets [nb], then the candidate count
+  int32_t* f_cnt = nullptr;   // candidate counts, one slot per filter call since the last s_min pass
 };
 
 struct RefVec {
@@ -87,6 +87,7 @@ struct fr_ctx_s {
   std::string err;
   // entropy filter / MLP workspace (canonical element order)
   int64_t n_elem_total = 0;
+  int f_slot = -1;              // candidate counter of the current filter call (compute_smin starts over)
   int32_t* f_k = nullptr;
   int32_t* f_evals = nullptr;
   int32_t* f_flag = nullptr;
@@ -768,7 +769,7 @@ fr_status filter_alloc(fr_ctx c) {
   const int64_t n = c->n_elem_total;
   for (auto& b : c->blocks)
     if (dalloc(c, &b.sown, b.E) || dalloc(c, &b.smin, b.E) || dalloc(c, &b.f_det, b.n) ||
-        dalloc(c, &b.f_list, b.n) || dalloc(c, &b.f_cnt, (b.n + 255) / 256 + 1))
+        dalloc(c, &b.f_list, b.n) || dalloc(c, &b.f_cnt, FILT_SLOTS))
       return FR_ERR_ALLOC;
   if (dalloc(c, &c->f_k, n) || dalloc(c, &c->f_evals, n) || dalloc(c, &c->f_flag, n) ||
       dalloc(c, &c->f_feat, n * 16) || dalloc(c, &c->f_khat, n))
@@ -805,24 +806,26 @@ void hex_smin_p(fr_ctx c, DevBlock& b, const double* uprev) {
   const int g = (int)((b.n + 255) / 256);
   unsigned long long* sown = (unsigned long long*)b.sown;
   int pk = c->prof_begin("filter_smin");
-  k_fill_u64<<<grid_for(b.n, 256), 256, 0, c->stream>>>(sown, b.n, 0xFFF0000000000000ULL);   // ord_bits(+inf)
   hex_sown<P><<<(unsigned)(b.E / HexTileCfg<P>::NE), HexTileCfg<P>::NT, 0, c->stream>>>(
       uprev + b.native_off, sown, b.E, b.n, K, c->prm.gamma);
-  elem_smin<<<g, 256, 0, c->stream>>>(sown, b.nbr_elem, b.nfaces, b.smin, b.E, b.n);
+  elem_smin<<<g, 256, 0, c->stream>>>(sown, b.nbr_elem, b.nfaces, b.smin, b.E, b.n, b.f_det, b.f_cnt);
   c->prof_end(pk);
 }
 
-// Candidates of the search: detection at zeta = 0 and ordered compaction into
-// b.f_list / count b.f_cnt[nb]; untouched elements get k = 0 and one evaluation.
+// The candidate list of the current filter call on block b.
+CandList cand_list(fr_ctx c, const DevBlock& b) {
+  return CandList{b.f_list, b.f_cnt + c->f_slot, b.f_det, c->f_k + b.elem_off, c->f_evals + b.elem_off,
+                  c->f_slot + 1, b.n};
+}
+
+// Candidates of the search: detection at zeta = 0 into b.f_list / count b.f_cnt[slot];
+// untouched elements get k = 0 and one evaluation.
 template <int P>
 void hex_candidates_p(fr_ctx c, DevBlock& b, const double* u, const StageFuse* fz = nullptr) {
   const FiltK K = filtk_of(c->host.hex);
   const FiltPrm F = filtprm_of(c->prm, P);
-  const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
-  const int gf = grid_for(b.n, 256);
+  const CandList L = cand_list(c, b);
   int pk = c->prof_begin(fz ? "rk4_stage_filter_detect_hex" : "filter_detect");
-  k_filter_reset<<<gf, 256, 0, c->stream>>>(b.f_det, c->f_k + o, c->f_evals + o, b.n);
   if constexpr (P == 4) {
     // p = 4: a tile holds only 8 elements, so the tiled pass would move its rows in
     // 64-byte segments; one wave per (64-element tile, column) reads whole 512-byte rows
@@ -832,33 +835,30 @@ void hex_candidates_p(fr_ctx c, DevBlock& b, const double* u, const StageFuse* f
     const unsigned g = (unsigned)((b.E / 64 * (P + 1) * (P + 1) + 3) / 4);
     if (!fz)
       hex_filter_detect_lines<P, PlainSrc><<<g, 256, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E,
-                                                                     b.n, K, F, b.f_det);
+                                                                     b.n, K, F, L);
     else if (fz->k32)
       hex_filter_detect_lines<P, RkStageSrc<float>><<<g, 256, 0, c->stream>>>(stage_src<float>(*fz, b, c->prm),
-                                                                              b.smin, b.E, b.n, K, F, b.f_det);
+                                                                              b.smin, b.E, b.n, K, F, L);
     else
       hex_filter_detect_lines<P, RkStageSrc<double>><<<g, 256, 0, c->stream>>>(stage_src<double>(*fz, b, c->prm),
-                                                                               b.smin, b.E, b.n, K, F, b.f_det);
+                                                                               b.smin, b.E, b.n, K, F, L);
   } else {
     const unsigned g = (unsigned)(b.E / HexTileCfg<P>::NE);
     if (!fz)
       hex_filter_detect<P, PlainSrc><<<g, HexTileCfg<P>::NT, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin,
-                                                                             b.E, b.n, K, F, b.f_det, nullptr);
+                                                                             b.E, b.n, K, F, L, nullptr);
     else if (fz->k32)
       hex_filter_detect<P, RkStageSrc<float>><<<g, HexTileCfg<P>::NT, 0, c->stream>>>(
-          stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, b.f_det,
+          stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, L,
           fz->cand64 ? fz->cand64 + b.native_off : nullptr);
     else
       hex_filter_detect<P, RkStageSrc<double>><<<g, HexTileCfg<P>::NT, 0, c->stream>>>(
-          stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, b.f_det,
+          stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, L,
           fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   }
-  k_flag_count<<<nb, 256, 0, c->stream>>>(b.f_det, b.n, b.f_cnt);
-  k_scan_counts<<<1, 1024, 0, c->stream>>>(b.f_cnt, nb);
-  k_flag_scatter<<<nb, 256, 0, c->stream>>>(b.f_det, b.n, b.f_cnt, b.f_list);
   if (P == 4 && fz && fz->cand64 && fz->k32)
     k_cand_stage<float><<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(b.n, 4096)), 256, 0, c->stream>>>(
-        stage_src<float>(*fz, b, c->prm), b.f_list, b.f_cnt + nb, b.nsp * 5, b.E, fz->cand64 + b.native_off);
+        stage_src<float>(*fz, b, c->prm), b.f_list, b.f_cnt + c->f_slot, b.nsp * 5, b.E, fz->cand64 + b.native_off);
   c->prof_end(pk);
 }
 
@@ -873,10 +873,9 @@ void hex_features_p(fr_ctx c, DevBlock& b, const double* u) {
   const FiltK K = filtk_of(c->host.hex);
   const FiltPrm F = filtprm_of(c->prm, P);
   const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
   k_fill_i32<<<grid_for(b.n, 256), 256, 0, c->stream>>>(c->f_flag + o, b.n, 0);
   constexpr int FW = HexFW<P>::value;
-  hex_features<P><<<list_grid(b, FW), 64 * FW, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + nb, K, F,
+  hex_features<P><<<list_grid(b, FW), 64 * FW, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + c->f_slot, K, F,
                                                        c->f_flag + o, c->f_feat + o * 16);
 }
 
@@ -886,7 +885,6 @@ void hex_filter_p(fr_ctx c, DevBlock& b, double* u, int mode, float* u32, const 
   const FiltK K = filtk_of(c->host.hex);
   const FiltPrm F = filtprm_of(c->prm, P);
   const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
   Dev32 s32{u32 ? u32 + b.native_off : nullptr, {0, 0, 0, 0, 0}};
   for (int v = 0; v < 5; ++v) s32.ref[v] = c->prm.u_ref[v];
   hex_candidates_p<P>(c, b, u, fz);
@@ -894,12 +892,12 @@ void hex_filter_p(fr_ctx c, DevBlock& b, double* u, int mode, float* u32, const 
   if (mode == 1) {
     pk = c->prof_begin("filter_search_learned");
     hex_filter_learned<P><<<list_grid(b, FW), 64 * FW, 0, c->stream>>>(
-        u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + nb, K, F, c->m_w, c->m_scale, c->f_k + o,
+        u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + c->f_slot, K, F, c->m_w, c->m_scale, c->f_k + o,
         c->f_evals + o, s32);
   } else {
     pk = c->prof_begin("filter_search_plain");
     hex_filter<P><<<list_grid(b, FW), 64 * FW, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list,
-                                                               b.f_cnt + nb, K, F, c->f_k + o, c->f_evals + o, s32);
+                                                               b.f_cnt + c->f_slot, K, F, c->f_k + o, c->f_evals + o, s32);
   }
   c->prof_end(pk);
 }
@@ -910,47 +908,40 @@ void tet_smin(fr_ctx c, DevBlock& b, const double* uprev) {
   unsigned long long* sown = (unsigned long long*)b.sown;
   int pk = c->prof_begin("filter_smin");
   tet_sown<<<(unsigned)(b.E / 64), TF_NT, 0, c->stream>>>(uprev + b.native_off, sown, b.E, b.n, c->prm.gamma);
-  elem_smin<<<g, 256, 0, c->stream>>>(sown, b.nbr_elem, b.nfaces, b.smin, b.E, b.n);
+  elem_smin<<<g, 256, 0, c->stream>>>(sown, b.nbr_elem, b.nfaces, b.smin, b.E, b.n, b.f_det, b.f_cnt);
   c->prof_end(pk);
 }
 
 void tet_candidates(fr_ctx c, DevBlock& b, const double* u, const StageFuse* fz = nullptr) {
   const FiltPrm F = filtprm_of(c->prm, c->prm.order);
-  const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
+  const CandList L = cand_list(c, b);
   int pk = c->prof_begin(fz ? "rk4_stage_filter_detect_tet" : "filter_detect");
-  k_filter_reset<<<grid_for(b.n, 256), 256, 0, c->stream>>>(b.f_det, c->f_k + o, c->f_evals + o, b.n);
   const unsigned gE = (unsigned)(b.E / 64);
   if (!fz)
-    tet_filter_detect<PlainSrc><<<gE, TF_NT, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E, b.n, F, b.f_det,
+    tet_filter_detect<PlainSrc><<<gE, TF_NT, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E, b.n, F, L,
                                                            nullptr);
   else if (fz->k32)
     tet_filter_detect<RkStageSrc<float>><<<gE, TF_NT, 0, c->stream>>>(
-        stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, F, b.f_det,
+        stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, F, L,
         fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   else
     tet_filter_detect<RkStageSrc<double>><<<gE, TF_NT, 0, c->stream>>>(
-        stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, F, b.f_det,
+        stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, F, L,
         fz->cand64 ? fz->cand64 + b.native_off : nullptr);
-  k_flag_count<<<nb, 256, 0, c->stream>>>(b.f_det, b.n, b.f_cnt);
-  k_scan_counts<<<1, 1024, 0, c->stream>>>(b.f_cnt, nb);
-  k_flag_scatter<<<nb, 256, 0, c->stream>>>(b.f_det, b.n, b.f_cnt, b.f_list);
   c->prof_end(pk);
 }
 
 void tet_features_b(fr_ctx c, DevBlock& b, const double* u) {
   const FiltPrm F = filtprm_of(c->prm, c->prm.order);
   const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
   k_fill_i32<<<grid_for(b.n, 256), 256, 0, c->stream>>>(c->f_flag + o, b.n, 0);
-  tet_features<<<list_grid(b, 4), 256, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + nb,
+  tet_features<<<list_grid(b, 4), 256, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + c->f_slot,
                                                          c->tet_ftab, F, c->f_flag + o, c->f_feat + o * 16);
 }
 
 void tet_filter_b(fr_ctx c, DevBlock& b, double* u, int mode, float* u32, const StageFuse* fz) {
   const FiltPrm F = filtprm_of(c->prm, c->prm.order);
   const int64_t o = b.elem_off;
-  const int nb = (int)((b.n + 255) / 256);
   Dev32 s32{u32 ? u32 + b.native_off : nullptr, {0, 0, 0, 0, 0}};
   for (int v = 0; v < 5; ++v) s32.ref[v] = c->prm.u_ref[v];
   tet_candidates(c, b, u, fz);
@@ -958,17 +949,18 @@ void tet_filter_b(fr_ctx c, DevBlock& b, double* u, int mode, float* u32, const 
   if (mode == 1) {
     pk = c->prof_begin("filter_search_learned");
     tet_filter_learned<<<list_grid(b, 4), 256, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list,
-                                                                 b.f_cnt + nb, c->tet_ftab, F, c->m_w, c->m_scale,
+                                                                 b.f_cnt + c->f_slot, c->tet_ftab, F, c->m_w, c->m_scale,
                                                                  c->f_k + o, c->f_evals + o, s32);
   } else {
     pk = c->prof_begin("filter_search_plain");
-    tet_filter<<<list_grid(b, 4), 256, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + nb,
+    tet_filter<<<list_grid(b, 4), 256, 0, c->stream>>>(u + b.native_off, b.smin, b.E, b.f_list, b.f_cnt + c->f_slot,
                                                          c->tet_ftab, F, c->f_k + o, c->f_evals + o, s32);
   }
   c->prof_end(pk);
 }
 
 fr_status compute_smin(fr_ctx c, const double* uprev) {
+  c->f_slot = -1;
   for (auto& b : c->blocks) {
     if (b.etype == FR_TET) {
       tet_smin(c, b, uprev);
@@ -998,6 +990,7 @@ fr_status apply_filter(fr_ctx c, double* u, int mode, float* u32, const StageFus
     fr_status st = collect_rows(c, u);
     if (st) return st;
   }
+  if ((++c->f_slot) >= FILT_SLOTS) return fail(c, FR_ERR_STATE, "more filter calls per s_min pass than counters");
   for (auto& b : c->blocks) {
     if (b.etype == FR_TET) {
       tet_filter_b(c, b, u, mode, u32, fz);
@@ -1034,6 +1027,7 @@ void hex_candidate_features_p(fr_ctx c, DevBlock& b, const double* u) {
 }
 
 fr_status candidate_features(fr_ctx c, const double* u) {
+  if ((++c->f_slot) >= FILT_SLOTS) return fail(c, FR_ERR_STATE, "more filter calls per s_min pass than counters");
   for (auto& b : c->blocks) {
     if (b.etype == FR_TET) {
       tet_candidates(c, b, u);
@@ -1941,7 +1935,7 @@ fr_status fr_filter(fr_ctx c, void* u_, const void* uprev_, int32_t mode, int32_
     stats->seconds = ms * 1e-3;
     for (auto& b : c->blocks) {
       int32_t m = 0;
-      HIP_TRY(c, hipMemcpy(&m, b.f_cnt + (b.n + 255) / 256, 4, hipMemcpyDeviceToHost));
+      HIP_TRY(c, hipMemcpy(&m, b.f_cnt + c->f_slot, 4, hipMemcpyDeviceToHost));
       stats->n_candidates += m;
     }
   }
