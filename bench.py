@@ -160,12 +160,13 @@ def kernel_bytes_per_elem(name, nsp, nfp):
         "tet_grad": d * (5 * nsp + 15 * nsp) + tet_gc,
         "tet_div_ns": d * (5 * nsp + 15 * nsp + 5 * nsp) + tet_gc,
         # pyramids: traces of u stored for every flux point (read by both sides); with the
-        # one-sided switch the gradient traces are stored where the element is the right
-        # side (half of the flux points) and read from there by both sides
+        # one-sided switch the gradient kernel reads both traces where it forms the pair's
+        # common flux (half of the flux points) and stores that flux and S_i . f_v at the
+        # solution points, the divergence reads both (the flux at all of its flux points)
         "pyr_trace": d * 5 * (nsp + nfp),
         "pyr_div_euler": d * (5 * nsp + 5 * nfp + 5 * nsp) + pyr_gc,
-        "pyr_grad": d * (5 * nsp + 5 * nfp + 15 * nsp + 15 * nfp // 2) + pyr_gc,
-        "pyr_div_ns": d * (5 * nsp + 15 * nsp + 5 * nfp + 15 * nfp // 2 + 5 * nsp) + pyr_gc,
+        "pyr_grad": d * (5 * nsp + 5 * nfp + 12 * nsp + 5 * nfp // 2) + pyr_gc,
+        "pyr_div_ns": d * (5 * nsp + 12 * nsp + 5 * nfp + 5 * nsp) + pyr_gc,
     }
     if d == 4:
         # FP32 form, one-sided LDG: the gradient kernel stores the transformed viscous flux
@@ -184,7 +185,7 @@ def _family_hash(kernel, read):
     driver; the block loop that calls the drivers is left out).  read(name) returns the
     bytes of a file of csrc/."""
     hdr = {"tet_": ("tet.hpp", "hex.hpp", "physics.hpp"),
-           "pyr_": ("pyr.hpp", "hex.hpp", "physics.hpp")}.get(kernel[:4], ("hex.hpp", "physics.hpp"))
+           "pyr_": ("pyr.hpp", "tet.hpp", "hex.hpp", "physics.hpp")}.get(kernel[:4], ("hex.hpp", "physics.hpp"))
     h = hashlib.sha256()
     for f in hdr:
         h.update(read(f))

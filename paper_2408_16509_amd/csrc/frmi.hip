@@ -646,26 +646,42 @@ fr_status pyr_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
   T* uf = (T*)b.uf;
   static const std::string sfx = sizeof(T) == 8 ? "" : "_f32";
   if (b.E % 64 != 0) return fail(c, FR_ERR_STATE, "pyramid block not padded to 64 elements");
-  const unsigned nblk = (unsigned)(b.E / py_ne<T>());
-  int pk = c->prof_begin(("pyr_trace" + sfx).c_str());
-  pyr_trace<T><<<nblk, py_nt<T>(), 0, c->stream>>>(u, uf, b.E, O.It);
-  c->prof_end(pk);
   const T gam = (T)p.gamma, mu = (T)p.mu, pr = (T)p.prandtl, beta = (T)p.ldg_beta, tau = (T)p.ldg_tau;
   const int sm = side_mode_of(p.ldg_beta);
+  // the matrix-core form: Euler, and Navier--Stokes with a one-sided switch (a two-sided
+  // common flux needs both sides' gradient traces, which only the general form stores)
+  const T* mo = ops + 2 * PY_NSP * PY_NFP + 3 * PY_NSP * PY_NSP;
+  const PymOps<T> Q{mo, mo + PYM_KP * PYM_FM, mo + PYM_KP * PYM_FM + 3 * PYM_KP * PYM_M};
+  const unsigned nb16 = (unsigned)(b.E / PYM_NE);
+  int pk = c->prof_begin(("pyr_trace" + sfx).c_str());
+  pyr_trace_mma<T><<<nb16, 64 * PYM_FT, 0, c->stream>>>(u, uf, b.E, Q);
+  c->prof_end(pk);
   if (p.system == FR_EULER) {
     pk = c->prof_begin(("pyr_div_euler" + sfx).c_str());
-    pyr_div<T, DEV, false><<<nblk, py_nt<T>(), 0, c->stream>>>(u, uf, nullptr, nullptr, geo, C, O, K, r, b.E, gam,
-                                                                    mu, pr, beta, tau, p.riemann, 0, R);
+    pyr_div_mma<T, DEV, false><<<nb16, PYM_NT, 0, c->stream>>>(u, uf, nullptr, nullptr, geo, C, Q, K, r, b.E, b.n, gam,
+                                                               0, p.riemann, R);
+    c->prof_end(pk);
+  } else if (sm != 0) {
+    T* fv = (T*)b.grad;
+    T* fc = (T*)b.fc;
+    pk = c->prof_begin(("pyr_grad" + sfx).c_str());
+    pyr_grad_mma<T, DEV><<<nb16, PYM_NT, 0, c->stream>>>(u, uf, geo, C, Q, K, fv, fc, b.E, sm, gam, mu, pr, tau,
+                                                         p.riemann, R);
+    c->prof_end(pk);
+    pk = c->prof_begin(("pyr_div_ns" + sfx).c_str());
+    pyr_div_mma<T, DEV, true><<<nb16, PYM_NT, 0, c->stream>>>(u, uf, fv, fc, geo, C, Q, K, r, b.E, b.n, gam, sm,
+                                                              p.riemann, R);
     c->prof_end(pk);
   } else {
+    const unsigned nblk = (unsigned)(b.E / py_ne<T>());
     T* grad = (T*)b.grad;
     T* gradf = (T*)b.gradf;
     pk = c->prof_begin(("pyr_grad" + sfx).c_str());
-    pyr_grad<T><<<nblk, PY_NT, 0, c->stream>>>(u, uf, geo, C, O, K, grad, gradf, b.E, beta, sm);
+    pyr_grad<T><<<nblk, PY_NT, 0, c->stream>>>(u, uf, geo, C, O, K, grad, gradf, b.E, beta);
     c->prof_end(pk);
     pk = c->prof_begin(("pyr_div_ns" + sfx).c_str());
-    pyr_div<T, DEV, true><<<nblk, py_nt<T>(), 0, c->stream>>>(u, uf, grad, gradf, geo, C, O, K, r, b.E, gam, mu,
-                                                                   pr, beta, tau, p.riemann, sm, R);
+    pyr_div<T, DEV><<<nblk, py_nt<T>(), 0, c->stream>>>(u, uf, grad, gradf, geo, C, O, K, r, b.E, gam, mu, pr, beta,
+                                                        tau, p.riemann, R);
     c->prof_end(pk);
   }
   hipError_t e = hipGetLastError();
@@ -1402,7 +1418,32 @@ fr_status setup_impl(const fr_params* p, int64_t n_vert, const double* xyz, cons
   }
   if (std::any_of(c->blocks.begin(), c->blocks.end(), [](const DevBlock& b) { return b.etype == FR_PYR; })) {
     const PyrOps& Y = c->host.pyr;
-    std::vector<double> ops((size_t)PY_NSP * PY_NFP * 2 + 3 * PY_NSP * PY_NSP);
+    // the general kernels' operators, then the matrix-core kernels' (zero-padded)
+    const size_t pym0 = (size_t)PY_NSP * PY_NFP * 2 + 3 * PY_NSP * PY_NSP;
+    std::vector<double> ops(pym0 + (size_t)PYM_KP * PYM_FM + 3 * PYM_KP * PYM_M + PYM_KL * PYM_M, 0.0);
+    double* Im = ops.data() + pym0;
+    double* Dm = Im + PYM_KP * PYM_FM;
+    double* Lm = Dm + 3 * PYM_KP * PYM_M;
+    for (int f = 0; f < 5; ++f) {
+      // the flux tiles' layout and the sparsity of the normals that pyr_div_mma relies on
+      const int flat = f == 0 ? 0 : (f % 2 ? 0 : 1);
+      if (Y.face_off[f] != pym_off(f) || Y.face_off[f + 1] != pym_off(f + 1) || std::fabs(Y.nref[f][flat]) > 1e-14 ||
+          (f == 0 && std::fabs(Y.nref[0][1]) > 1e-14)) {
+        c->err = "pyramid faces not in the expected order";
+        return bail(FR_ERR_STATE);
+      }
+    }
+    for (int ft = 0; ft < PYM_FT; ++ft)
+      for (int row = 0; row < 16; ++row) {
+        const int fp = pym_fp(ft, row);
+        if (fp < 0) continue;
+        for (int j = 0; j < PY_NSP; ++j) Im[j * PYM_FM + 16 * ft + row] = Y.interp[fp][j];
+        const int f = pym_face(ft), k = pym_krow0(f) + fp - pym_off(f);
+        for (int pt = 0; pt < PY_NSP; ++pt) Lm[k * PYM_M + pt] = Y.lift[pt][fp];
+      }
+    for (int i = 0; i < 3; ++i)
+      for (int j = 0; j < PY_NSP; ++j)
+        for (int pt = 0; pt < PY_NSP; ++pt) Dm[(i * PYM_KP + j) * PYM_M + pt] = Y.D[i][pt][j];
     double* It = ops.data();
     double* Dt = It + PY_NSP * PY_NFP;
     double* Lt = Dt + 3 * PY_NSP * PY_NSP;
