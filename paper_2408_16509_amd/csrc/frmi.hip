@@ -593,16 +593,19 @@ fr_status tet_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
           R);
     c->prof_end(pk);
   } else {
-    // one-sided LDG (beta = +-1/2), FP32 form: the gradient kernel also forms the common
-    // fluxes (in FP64 the extra registers cost that kernel more than the divergence saves)
-    constexpr bool can_fc = sizeof(T) == 4;
+    // one-sided LDG (beta = +-1/2): the gradient kernel also forms the common fluxes, once
+    // per pair, and the divergence reads them (FP64, 24,480 tetrahedra: gradient 86 -> 105 us,
+    // divergence 137 -> 76).  Not for FP64 curved elements, whose two sides' stored normals
+    // agree to rounding only: one side's unit normal on both moved the low-Mach residual
+    // by 1e-9, beyond its rounding floor
+    constexpr bool can_fc = sizeof(T) == 4 || !CUR;
     const bool fc = sm != 0 && can_fc;
     T* fcb = (T*)b.fc;
     const T gam = (T)p.gamma, mu = (T)p.mu, pr = (T)p.prandtl, beta = (T)p.ldg_beta, tau = (T)p.ldg_tau;
     const T* ogT = (const T*)c->tet_ogT;
     pk = c->prof_begin(("tet_grad" + sfx).c_str());
 #define FR_TET_GRAD(BF, FCX)                                                                                   \
-  tet_grad_mma<T, DEV, BF, FCX, CUR><<<div_grid, tgr_nt<T>(), 0, c->stream>>>(u, geo, C, O, ogT, ogH, ogL, (T*)b.grad, fcb, \
+  tet_grad_mma<T, DEV, BF, FCX, CUR><<<div_grid, TGR_NT, 0, c->stream>>>(u, geo, C, O, ogT, ogH, ogL, (T*)b.grad, fcb, \
                                                                     b.E, b.n, beta, sm, gam, mu, pr, tau,       \
                                                                     p.riemann, R)
     if (bf3) {
@@ -620,7 +623,15 @@ fr_status tet_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
     if (bf3) {
       if (fc) FR_TET_DIV(can_bf3, can_fc); else FR_TET_DIV(can_bf3, false);
     } else {
-      if (fc) FR_TET_DIV(false, can_fc); else FR_TET_DIV(false, false);
+      if constexpr (sizeof(T) == 8 && !CUR) {
+        if (fc)
+          tet_div_fv<T><<<div_grid, 256, 0, c->stream>>>(u, (const T*)b.grad, fcb, geo, C, O, opT, r, b.E, b.n, gam, sm,
+                                                         R);
+        else
+          FR_TET_DIV(false, false);
+      } else {
+        if (fc) FR_TET_DIV(false, can_fc); else FR_TET_DIV(false, false);
+      }
     }
 #undef FR_TET_DIV
     c->prof_end(pk);

@@ -221,11 +221,10 @@ constexpr int TET_KA16 = 112, TET_KB16 = 64, TET_KP16 = TET_KA16 + TET_KB16;
 // also share the gathers (3.0 -> 2.65 ms per FP32 launch on the mixed workload against
 // five waves of which two only gather); in FP32 a fourth wave joins the gathers and the
 // flux evaluation (four blocks per CU either way, set by LDS: 1.286 -> 1.246 ms).  The
-// gradient gathers more (the common solution at all 60 flux points): four waves in
-// FP32 (three multiply; 2.95 -> 2.47 ms per launch against five), five in FP64 (four:
-// 5.7 ms against 3.85).
+// gradient gathers more (the common solution at all 60 flux points): four waves (three
+// multiply; FP32 2.95 -> 2.47 ms per launch against five).
 constexpr int TDIV_NE = 16;
-// Layout of the transformed viscous fluxes S_i . f_v that the FP32 gradient kernel stores
+// Layout of the transformed viscous fluxes S_i . f_v that the one-sided gradient kernel stores
 // for the divergence kernel (12 rows per solution point): tile by tile of NE elements,
 // [tile][pt * 12 + k][el], so the rows of one tile are contiguous and the two halves of
 // every 128-byte line are written by the same wave in consecutive stores (in the
@@ -235,7 +234,7 @@ template <int NE>
 __device__ __forceinline__ int64_t tet_fv_index(int64_t e0, int row, int el) {
   return e0 * (12 * TET_NSP) + (int64_t)row * NE + el;
 }
-// The same for the pair-once common fluxes of the FP32 one-sided form (5 rows per flux
+// The same for the pair-once common fluxes of the one-sided form (5 rows per flux
 // point, [tile][sg * 5 + c][el]); the divergence kernel also reads the partner's slot,
 // at element e of any tile.
 template <int NE>
@@ -244,8 +243,7 @@ __device__ __forceinline__ int64_t tet_fc_index(int64_t e, int row) {
 }
 template <typename T>
 constexpr int tdiv_nt() { return sizeof(T) == 4 ? 4 * 64 : 3 * 64; }
-template <typename T>
-constexpr int tgr_nt() { return sizeof(T) == 4 ? 4 * 64 : 5 * 64; }
+constexpr int TGR_NT = 4 * 64;
 
 // Corrected divergence (eq:FRfinal) on the matrix cores: per block of 16 elements,
 // R^T = -(1/J) Op P with the panel P = [f~_0; f~_1; f~_2; F^C] (K x 5*16).  A block
@@ -438,6 +436,107 @@ __global__ void __launch_bounds__(tdiv_nt<T>()) tet_div(const T* __restrict__ u,
   }
 }
 
+// The divergence of the FP64 form of straight elements with a one-sided switch: as tet_div
+// with FCIN, the transformed fluxes of one direction at a time through the panel (36 rows
+// instead of 108: 38 KB of LDS per block, set by the flux-point rows, against 70 KB, so that
+// four blocks of four waves share a CU instead of two of three).  Each thread keeps its
+// points' states in registers over the three directions; the next direction's viscous fluxes
+// load during the products.  24,480 tetrahedra: 84 us with tet_div's panel, 76 here (137 with
+// the common flux formed by both sides).
+template <typename T>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) tet_div_fv(
+    const T* __restrict__ u, const T* __restrict__ fv, const T* __restrict__ fcin, const T* __restrict__ geo, Conn C,
+    TetDev<T> O, const T* __restrict__ opT, T* __restrict__ r, int64_t E, int64_t n, T gamma, int side_mode,
+    RefState<T> R) {
+  constexpr int NE = TDIV_NE, NT = 256, NP = (TET_NSP * NE + NT - 1) / NT, NI = (NE * TET_NFP + NT - 1) / NT;
+  __shared__ T PAN[TET_NFP * 5 * NE];     // [row][v][el]
+  __shared__ T SJ[10 * NE];
+  const int t = threadIdx.x;
+  const int w = t / 64, lane = t % 64, col = lane % 16, tr = t / NE, tel = t % NE;
+  const int mt[1] = {w};
+  const int64_t e0 = xcd_block() * NE;
+  T wv[NP][5], fn[NP][4];
+  auto load_fv = [&](int i) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const int pt = min(tr + j * (NT / NE), TET_NSP - 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) fn[j][c] = fv[tet_fv_index<NE>(e0, pt * 12 + i * 4 + c, tel)];
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < NP; ++j) tet_load(u, E, e0 + tel, min(tr + j * (NT / NE), TET_NSP - 1), wv[j]);
+  load_fv(0);
+  for (int i = t; i < 10 * NE; i += NT) SJ[i] = geo[(int64_t)(i / NE) * E + e0 + i % NE];
+  for (int i = t; i < 5 * NE; i += NT) PAN[TET_NSP * 5 * NE + i] = T(0);      // row 35 of a direction
+  __syncthreads();
+  typename Mma16<T>::V acc[1][5];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) acc[0][v] = typename Mma16<T>::V{0, 0, 0, 0};
+  int inf[NI], nel[NI];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    T s[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = SJ[(3 * i + j) * NE + tel];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const int pt = tr + j * (NT / NE);
+      if (pt >= TET_NSP) continue;
+      T f[5];
+      PointInv<T, false>(wv[j], gamma, R).dir(s[0], s[1], s[2], f);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) PAN[(pt * 5 + c) * NE + tel] = c == 0 ? f[0] : f[c] - fn[j][c - 1];
+    }
+    if (i < 2) {
+      load_fv(i + 1);
+    } else {
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        const int row = min(tr + j * (NT / NE), TET_NFP - 1);
+        const int64_t o = (int64_t)(row / TET_NFPF) * E + e0 + tel;
+        inf[j] = C.nbr_info[o];
+        nel[j] = C.nbr_elem[o];
+      }
+    }
+    __syncthreads();
+    if (w < 3)
+      tet_contract<T, false, 1, NE>(acc, PAN, TET_NSP + 1, lane, opT, i * TET_NSP, TET_MP, mt, nullptr, nullptr, 0);
+    __syncthreads();
+  }
+  // the common fluxes at the flux points, from the slot of the side that formed each
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int sg = tr + j * (NT / NE);
+    if (sg >= TET_NFP) continue;
+    const int nf = inf[j] & 7, orient = (inf[j] >> 3) & 511;
+    const bool left = (inf[j] >> 12) & 1, own = left != (side_mode > 0);
+    const int64_t fe = own ? e0 + tel : (int64_t)nel[j];
+    const int fp = own ? sg : nf * TET_NFPF + C.perm[orient * C.perm_stride + sg % TET_NFPF];
+    T S[9], nv[3];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) S[k] = SJ[k * NE + tel];
+    tet_normal(S, O, sg / TET_NFPF, nv);
+    const T mag = fsqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
+    const T fs = left ? mag : -mag;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) PAN[(sg * 5 + c) * NE + tel] = fcin[tet_fc_index<NE>(fe, fp * 5 + c)] * fs;
+  }
+  __syncthreads();
+  if (w >= 3) return;
+  tet_contract<T, false, 1, NE>(acc, PAN, TET_KB, lane, opT, TET_KA, TET_MP, mt, nullptr, nullptr, 0);
+  const int64_t e = e0 + col;
+  const T iJ = -rcp(SJ[9 * NE + col]);
+  if (e >= n) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int pt = w * 16 + Mma16<T>::row(lane, q);
+    if (pt >= TET_NSP) continue;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) r[((int64_t)pt * 5 + v) * E + e] = acc[0][v][q] * iJ;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Output rows of the gradient product (per direction 48 = 3 point tiles of 16) hold the
 // solution points in an order chosen at setup (TetDev::slot): the points that carry the
@@ -453,7 +552,8 @@ __global__ void __launch_bounds__(tdiv_nt<T>()) tet_div(const T* __restrict__ u,
 // gt_i of a point meet in one lane, where the physical gradient S^T gt / J is formed
 // and stored; each operator value the wave loads serves five products.
 //
-// FC (one-sided LDG, beta = +-1/2, side_mode = sign of beta): the common flux of
+// FC (one-sided LDG, beta = +-1/2, side_mode = sign of beta; FP32, and FP64 on straight
+// elements): the common flux of
 // every flux-point pair is formed here, once, by the element whose gradient the
 // viscous part takes (the right side for beta = 1/2), and stored in that element's
 // slot of fc; the divergence kernel reads it from there for both sides and scales it
@@ -515,13 +615,13 @@ __device__ __forceinline__ void tet_grad_contract(typename Mma16<T>::V (&acc)[3]
 }
 
 template <typename T, bool DEV, bool BF3, bool FC, bool CUR = false>
-__global__ void __launch_bounds__(tgr_nt<T>()) __attribute__((amdgpu_waves_per_eu(4))) tet_grad_mma(const T* __restrict__ u, const T* __restrict__ geo, Conn C,
+__global__ void __launch_bounds__(TGR_NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) tet_grad_mma(const T* __restrict__ u, const T* __restrict__ geo, Conn C,
                                                         TetDev<T> O, const T* __restrict__ ogT,
                                                         const tet_s4* __restrict__ ogH, const tet_s4* __restrict__ ogL,
                                                         T* __restrict__ grad, T* __restrict__ fc, int64_t E, int64_t n,
                                                         T beta, int side_mode, T gamma, T mu, T pr, T tau, int riemann,
                                                         RefState<T> R) {
-  constexpr int NE = TDIV_NE, NT = tgr_nt<T>();
+  constexpr int NE = TDIV_NE, NT = TGR_NT;
   constexpr int KR = BF3 ? TGR_K : TGS_K;
   // [k][v][el]: u at the 35 points, u^ at the 60 flux points (BF16x3: rows 35..94; else
   // face by face, tgs_row), zero rows
