@@ -485,41 +485,79 @@ pyr_grad_mma(const T* __restrict__ u, const T* __restrict__ uf,
   __shared__ T SJ[10 * NE];
   const int t = threadIdx.x, w = t / 64, lane = t % 64, kr = lane / 16, col = lane % 16;
   const int64_t e0 = xcd_block() * NE, e = e0 + col;
-  for (int i = t; i < 10 * NE; i += NT) SJ[i] = geo[(int64_t)(i / NE) * E + e0 + i % NE];
+  // the gather in three rounds of loads (connectivity and states, point permutation, traces),
+  // each issued for all of the thread's items before any is used: with one item after the
+  // other a block spent 9.7 of its 36 us here
+  constexpr int NU = (5 * PY_NSP * NE + NT - 1) / NT, NJ = (PY_NFP * NE + NT - 1) / NT;
+  const int tel = t % NE, tr = t / NE;
+  static_assert(NT % NE == 0, "rows per pass");
+  int inf[NJ], nel[NJ], fac[NJ];
 #pragma unroll
-  for (int j = 0; j < (5 * PY_NSP * NE + NT - 1) / NT; ++j) {
-    const int i = t + j * NT;
-    if (i < 5 * PY_NSP * NE) W[i] = u[(int64_t)(i / NE) * E + e0 + i % NE];
+  for (int j = 0; j < NJ; ++j) {
+    const int fp = min(tr + j * (NT / NE), PY_NFP - 1);
+    fac[j] = fp < 25 ? 0 : 1 + (fp - 25) / 15;
+    inf[j] = C.nbr_info[(int64_t)fac[j] * E + e0 + tel];
+    nel[j] = C.nbr_elem[(int64_t)fac[j] * E + e0 + tel];
+  }
+  T ur[NU];
+#pragma unroll
+  for (int j = 0; j < NU; ++j)
+    ur[j] = u[(int64_t)min(tr + j * (NT / NE), 5 * PY_NSP - 1) * E + e0 + tel];
+  for (int i = t; i < 10 * NE; i += NT) SJ[i] = geo[(int64_t)(i / NE) * E + e0 + i % NE];
+  int fpn[NJ];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int fp = min(tr + j * (NT / NE), PY_NFP - 1);
+    fpn[j] = pym_off(inf[j] & 7) + C.perm[((inf[j] >> 3) & 511) * C.perm_stride + fp - pym_off(fac[j])];
   }
   // jump of the common solution: the partner's trace minus the own one where the switch
   // names the partner's side, else zero
+  T jm[NJ][5];
 #pragma unroll
-  for (int j = 0; j < (PY_NFP * NE + NT - 1) / NT; ++j) {
-    const int it = t + j * NT;
-    if (it >= PY_NFP * NE) continue;
-    const int el = it % NE, fp = it / NE;
-    int f, fpn;
-    int64_t en;
-    bool left;
-    pyr_partner(C, K, E, e0 + el, fp, f, en, fpn, left);
-    const bool formed = left != (side_mode > 0);
-    T* J = &W[JO + (pym_krow0(f) + fp - pym_off(f)) * 5 * NE + el];
+  for (int j = 0; j < NJ; ++j) {
+    const int fp = min(tr + j * (NT / NE), PY_NFP - 1);
+    const bool formed = (((inf[j] >> 12) & 1) != 0) != (side_mode > 0);
+    // not formed: both addresses the own trace, a zero jump from one line
+    const int64_t o = (int64_t)fp * 5 * E + e0 + tel, p = formed ? (int64_t)fpn[j] * 5 * E + nel[j] : o;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) jm[j][v] = uf[p + v * E] - uf[o + v * E];
+    if (!formed) {
+#pragma unroll
+      for (int v = 0; v < 5; ++v) jm[j][v] = T(0);     // also where a trace is not finite
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NU; ++j) {
+    const int i = t + j * NT;
+    if (i < 5 * PY_NSP * NE) W[i] = ur[j];
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int fp = tr + j * (NT / NE);
+    if (fp >= PY_NFP) continue;
 #pragma unroll
     for (int v = 0; v < 5; ++v)
-      J[v * NE] = formed ? uf[((int64_t)fpn * 5 + v) * E + en] - uf[((int64_t)fp * 5 + v) * E + e0 + el] : T(0);
+      W[JO + ((pym_krow0(fac[j]) + fp - pym_off(fac[j])) * 5 + v) * NE + tel] = jm[j][v];
   }
   for (int i = t; i < 7 * 5 * NE; i += NT) {           // padding rows 25, 26, 27 and one per triangle
     const int r = i / (5 * NE);
     W[JO + (r < 3 ? 25 + r : 28 + 16 * (r - 3) + 15) * 5 * NE + i % (5 * NE)] = T(0);
   }
   __syncthreads();
-  // reference gradient of point tile w, all variables
+  // reference gradient of point tile w, all variables (FP64: the lift's operator values load
+  // during the derivatives; FP32 has no registers for them at three waves per SIMD)
+  constexpr bool kAhead = sizeof(T) == 8;
+  T la[kAhead ? PYM_KL / 4 : 1];
+  if constexpr (kAhead) {
+#pragma unroll
+    for (int s = 0; s < PYM_KL / 4; ++s) la[s] = O.Lt[(4 * s + kr) * PYM_M + 16 * w + col];
+  }
   typename M::V gt[3][5];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int v = 0; v < 5; ++v) gt[i][v] = typename M::V{0, 0, 0, 0};
-#pragma unroll 2
+#pragma unroll 7
   for (int k0 = 0; k0 < PYM_KP; k0 += 4) {
     const int k = min(k0 + kr, PY_NSP - 1);
     T b[5];
@@ -541,7 +579,7 @@ pyr_grad_mma(const T* __restrict__ u, const T* __restrict__ uf,
 #pragma unroll
     for (int s = 0; s < (f == 0 ? 7 : 4); ++s) {
       const int k = pym_krow0(f) + 4 * s + kr;
-      const T a = O.Lt[k * PYM_M + 16 * w + col];
+      const T a = kAhead ? la[kAhead ? pym_krow0(f) / 4 + s : 0] : O.Lt[k * PYM_M + 16 * w + col];
 #pragma unroll
       for (int v = 0; v < 5; ++v) sf[v] = M::run(a, W[JO + (k * 5 + v) * NE + col], sf[v]);
     }
@@ -589,17 +627,38 @@ pyr_grad_mma(const T* __restrict__ u, const T* __restrict__ uf,
     const int64_t en = C.nbr_elem[(int64_t)f * E + e];
     const bool left = (info >> 12) & 1, formed = left != (side_mode > 0);
     if (!__any(formed)) continue;
+    // both sides' traces: FP64 loads them during the products, FP32 after (padding rows keep
+    // in-bounds addresses)
     const int fb = info & 7, orient = (info >> 3) & 511;
+    int fps[4], fpn[4];
+    T uo[4][5], un[4][5];
+    auto load_traces = [&] {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 5; ++v) {
+          uo[q][v] = uf[((int64_t)fps[q] * 5 + v) * E + e];
+          un[q][v] = uf[((int64_t)fpn[q] * 5 + v) * E + en];
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int fp = pym_fp(ft, M::row(lane, q));
+      fps[q] = fp < 0 ? pym_off(f) : fp;
+      fpn[q] = pym_off(fb) + C.perm[orient * C.perm_stride + fps[q] - pym_off(f)];
+    }
+    if constexpr (kAhead) load_traces();
     typename M::V gf[15];
 #pragma unroll
     for (int c = 0; c < 15; ++c) gf[c] = typename M::V{0, 0, 0, 0};
-#pragma unroll 2
+#pragma unroll (sizeof(T) == 8 ? 14 : 7)
     for (int k0 = 0; k0 < PYM_KP; k0 += 4) {
       const int k = min(k0 + kr, PY_NSP - 1);
       const T a = O.It[(k0 + kr) * PYM_FM + 16 * ft + col];
 #pragma unroll
       for (int c = 0; c < 15; ++c) gf[c] = M::run(a, W[(k * 15 + c) * NE + col], gf[c]);
     }
+    if constexpr (!kAhead) load_traces();
     if (!formed) continue;
     T nv[3], nL[3];
 #pragma unroll
@@ -609,23 +668,19 @@ pyr_grad_mma(const T* __restrict__ u, const T* __restrict__ uf,
     for (int j = 0; j < 3; ++j) nL[j] = nv[j] * sl;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int fp = pym_fp(ft, M::row(lane, q));
-      if (fp < 0) continue;
-      const int fpn = pym_off(fb) + C.perm[orient * C.perm_stride + fp - pym_off(f)];
-      T uo[5], un[5], uL[5], uR[5], g[15], F[5], f5[5];
+      if (pym_fp(ft, M::row(lane, q)) < 0) continue;
+      T uL[5], uR[5], g[15], F[5], f5[5];
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
-        uo[v] = uf[((int64_t)fp * 5 + v) * E + e];
-        un[v] = uf[((int64_t)fpn * 5 + v) * E + en];
-        uL[v] = left ? uo[v] : un[v];
-        uR[v] = left ? un[v] : uo[v];
+        uL[v] = left ? uo[q][v] : un[q][v];
+        uR[v] = left ? un[q][v] : uo[q][v];
       }
 #pragma unroll
       for (int c = 0; c < 15; ++c) g[c] = gf[c][q];
       common_inviscid<T, DEV>(riemann, uL, uR, nL, gamma, R, F);
-      viscous<T, DEV>(uo, g, nL[0], nL[1], nL[2], gamma, mu, pr, R, f5);
+      viscous<T, DEV>(uo[q], g, nL[0], nL[1], nL[2], gamma, mu, pr, R, f5);
 #pragma unroll
-      for (int v = 0; v < 5; ++v) fc[pym_fc_index(e, fp * 5 + v)] = F[v] - f5[v] + tau * (uL[v] - uR[v]);
+      for (int v = 0; v < 5; ++v) fc[pym_fc_index(e, fps[q] * 5 + v)] = F[v] - f5[v] + tau * (uL[v] - uR[v]);
     }
   }
 }
@@ -733,7 +788,7 @@ __global__ void __launch_bounds__(PYM_NT) pyr_div_mma(const T* __restrict__ u, c
     for (int v = 0; v < 5; ++v) acc[v] = typename M::V{0, 0, 0, 0};
     const int hd = f == 0 ? 2 : (f % 2 ? 1 : 0);       // the horizontal axis of the face's normal
     const T nh = f == 0 ? T(0) : K.nref[f][hd], nz = K.nref[f][2];
-#pragma unroll 2
+#pragma unroll
     for (int k0 = 0; k0 < PYM_KP; k0 += 4) {
       const int k = min(k0 + kr, PY_NSP - 1);
       const T o = O.It[(k0 + kr) * PYM_FM + 16 * ft + col];
@@ -754,7 +809,7 @@ __global__ void __launch_bounds__(PYM_NT) pyr_div_mma(const T* __restrict__ u, c
   for (int v = 0; v < 5; ++v) acc[v] = typename M::V{0, 0, 0, 0};
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-#pragma unroll 2
+#pragma unroll 14
     for (int k0 = 0; k0 < PYM_KP; k0 += 4) {
       const int k = i * PY_NSP + min(k0 + kr, PY_NSP - 1);
       const T a = O.Dt[(i * PYM_KP + k0 + kr) * PYM_M + 16 * w + col];
@@ -777,7 +832,7 @@ __global__ void __launch_bounds__(PYM_NT) pyr_div_mma(const T* __restrict__ u, c
     }
   }
   __syncthreads();
-#pragma unroll 2
+#pragma unroll
   for (int k0 = 0; k0 < PYM_KL; k0 += 4) {
     const T a = O.Lt[(k0 + kr) * PYM_M + 16 * w + col];
 #pragma unroll
