@@ -94,10 +94,9 @@ struct fr_ctx_s {
   float* f_feat = nullptr;
   float* f_khat = nullptr;
   double* f_copy = nullptr;     // FP64 native state copy (training targets)
-  float* m_w = nullptr;         // MLP parameters, Adam moments, gradient, input scaling
+  float* m_w = nullptr;         // MLP parameters, Adam moments, input scaling
   float* m_m = nullptr;
   float* m_v = nullptr;
-  float* m_g = nullptr;
   float* m_scale = nullptr;
   float* m_loss = nullptr;
   float* m_scratch = nullptr;
@@ -1104,7 +1103,7 @@ fr_status collect_rows(fr_ctx c, const double* u) {
 fr_status mlp_alloc(fr_ctx c, int batch) {
   if (!c->m_w) {
     if (dalloc(c, &c->m_w, MLP_NP) || dalloc(c, &c->m_m, MLP_NP) || dalloc(c, &c->m_v, MLP_NP) ||
-        dalloc(c, &c->m_g, MLP_NP) || dalloc(c, &c->m_scale, 2 * MLP_IN) || dalloc(c, &c->m_loss, 1))
+        dalloc(c, &c->m_scale, 2 * MLP_IN) || dalloc(c, &c->m_loss, 1))
       return FR_ERR_ALLOC;
   }
   if (batch > c->m_batch_cap) {
@@ -1167,7 +1166,7 @@ void fr_destroy(fr_ctx c) {
     (void)hipFree(b.f_det); (void)hipFree(b.f_list); (void)hipFree(b.f_cnt);
   }
   for (void* q : {(void*)c->f_k, (void*)c->f_evals, (void*)c->f_flag, (void*)c->f_feat, (void*)c->f_khat,
-                  (void*)c->f_copy, (void*)c->m_w, (void*)c->m_m, (void*)c->m_v, (void*)c->m_g, (void*)c->m_scale,
+                  (void*)c->f_copy, (void*)c->m_w, (void*)c->m_m, (void*)c->m_v, (void*)c->m_scale,
                   (void*)c->m_loss, (void*)c->m_scratch, (void*)c->m_sqerr, (void*)c->m_idx})
     (void)hipFree(q);
   c->prof_clear();
@@ -2086,8 +2085,8 @@ fr_status fr_mlp_grad(fr_ctx c, const float* x, const float* y, int64_t n, float
   if ((st = mlp_alloc(c, (int)n))) return st;
   mlp_fwd_bwd<<<(unsigned)((n + MLP_FB_WAVES - 1) / MLP_FB_WAVES), 64 * MLP_FB_WAVES, 0, c->stream>>>(
       c->m_w, c->m_scale, x, y, nullptr, (int)n, c->m_scratch, c->m_sqerr);
-  mlp_grad_reduce<<<(MLP_NP + 1 + MLP_GR_NT - 1) / MLP_GR_NT, MLP_GR_NT, 0, c->stream>>>(c->m_scratch, (int)n,
-                                                                                        c->m_sqerr, grad, loss);
+  mlp_grad_reduce<false><<<MLP_NP / MLP_GR_P + 1, MLP_GR_NT, 0, c->stream>>>(c->m_scratch, (int)n, c->m_sqerr, grad,
+                                                                            loss, AdamArgs{});
   HIP_TRY(c, hipGetLastError());
   return FR_OK;
 }
@@ -2102,8 +2101,7 @@ fr_status fr_mlp_grad_static(fr_ctx c, const float* x, const float* y, int64_t n
   float* sq = S + (int64_t)FR_MLP_STATIC_MAX_BATCH * MLP_SS;
   mlp_fwd_bwd<<<(unsigned)((n + MLP_FB_WAVES - 1) / MLP_FB_WAVES), 64 * MLP_FB_WAVES, 0, c->stream>>>(
       c->m_w, c->m_scale, x, y, nullptr, (int)n, S, sq);
-  mlp_grad_reduce<<<(MLP_NP + 1 + MLP_GR_NT - 1) / MLP_GR_NT, MLP_GR_NT, 0, c->stream>>>(S, (int)n, sq, grad,
-                                                                                        loss);
+  mlp_grad_reduce<false><<<MLP_NP / MLP_GR_P + 1, MLP_GR_NT, 0, c->stream>>>(S, (int)n, sq, grad, loss, AdamArgs{});
   HIP_TRY(c, hipGetLastError());
   return FR_OK;
 }
@@ -2120,9 +2118,9 @@ fr_status fr_mlp_train(fr_ctx c, const float* x, const float* y, int64_t n, cons
   for (int t = 1; t <= n_steps; ++t) {
     mlp_fwd_bwd<<<(unsigned)((batch + MLP_FB_WAVES - 1) / MLP_FB_WAVES), 64 * MLP_FB_WAVES, 0, c->stream>>>(
         c->m_w, c->m_scale, x, y, perm + (int64_t)(t - 1) * batch, batch, c->m_scratch, c->m_sqerr);
-    mlp_grad_reduce<<<(MLP_NP + 1 + MLP_GR_NT - 1) / MLP_GR_NT, MLP_GR_NT, 0, c->stream>>>(
-        c->m_scratch, batch, c->m_sqerr, c->m_g, loss_hist ? loss_hist + (t - 1) : c->m_loss);
-    mlp_adam<<<(MLP_NP + 255) / 256, 256, 0, c->stream>>>(c->m_w, c->m_g, c->m_m, c->m_v, t, lr, b1, b2, eps);
+    const AdamArgs A{c->m_w, c->m_m, c->m_v, lr, b1, b2, eps, 1.0f - std::pow(b1, (float)t), 1.0f - std::pow(b2, (float)t)};
+    mlp_grad_reduce<true><<<MLP_NP / MLP_GR_P + 1, MLP_GR_NT, 0, c->stream>>>(
+        c->m_scratch, batch, c->m_sqerr, nullptr, loss_hist ? loss_hist + (t - 1) : c->m_loss, A);
   }
   HIP_TRY(c, hipGetLastError());
   return FR_OK;
