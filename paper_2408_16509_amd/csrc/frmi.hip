@@ -565,6 +565,7 @@ fr_status tet_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
   O.src = c->tet_src;
   O.pfp = c->tet_src + 60;
   O.slot = c->tet_src + 60 + 35 * 4;
+  O.psrc = (const uint8_t*)(c->tet_src + 60 + 35 * 4 + TET_MP);
   for (int f = 0; f < 4; ++f)
     for (int k = 0; k < 3; ++k) O.nref[f][k] = (T)c->host.tet.nref[f][k];
   const RefState<T> R = ref_of<T>(p);
@@ -1419,6 +1420,21 @@ fr_status setup_impl(const fr_params* p, int64_t n_vert, const double* xyz, cons
         hipMemcpy(c->tet_ogT, bog.data(), bog.size(), hipMemcpyHostToDevice) != hipSuccess) {
       c->err = "tet operator upload failed";
       return bail(FR_ERR_DEVICE);
+    }
+    // per orientation and partner face: the partner's solution point of each flux point of
+    // the face (bytes, behind the other tables); orientations of hexahedral faces unused
+    {
+      const int no = c->host.n_orient, st = c->host.perm_stride;
+      std::vector<uint8_t> ps((size_t)no * 4 * 16, 0);
+      for (int o = 0; o < no; ++o)
+        for (int f = 0; f < 4; ++f)
+          for (int q = 0; q < TET_NFPF && q < st; ++q) {
+            const int pq = c->host.orient_perm[(size_t)o * st + q];
+            if (pq >= 0 && pq < TET_NFPF) ps[((size_t)o * 4 + f) * 16 + q] = (uint8_t)T.fp_src[f * TET_NFPF + pq];
+          }
+      const size_t n0 = src.size();
+      src.resize(n0 + ps.size() / 4);
+      std::memcpy(&src[n0], ps.data(), ps.size());
     }
     if (dalloc(c, &c->tet_src, src.size())) return bail(FR_ERR_ALLOC);
     if (hipMemcpy(c->tet_src, src.data(), src.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
