@@ -83,6 +83,7 @@ struct fr_ctx_s {
   void* rk_stage = nullptr;
   double* rk_acc = nullptr;
   void* rk_k = nullptr;
+  float* rk_kk = nullptr;       // FP32 form: the increments of stages 1..3
   int* flag = nullptr;
   std::string err;
   // entropy filter / MLP workspace (canonical element order)
@@ -422,43 +423,46 @@ __global__ void __launch_bounds__(256) k_err_sumsq(const double* __restrict__ Er
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// RK stages of the FP32 form: FP64 state and accumulator, FP32 increments and stage deviations.
-__global__ void k_rk32_first(const double* __restrict__ u, const float* __restrict__ k, double* __restrict__ acc,
-                             float* __restrict__ st, int64_t n, int64_t E, double b, double c, RefVec ref) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double ui = u[i], ki = (double)k[i];
-    acc[i] = ui + b * ki;
-    st[i] = (float)(ui + c * ki - ref.v[(i / E) % 5]);
-  }
-}
-__global__ void k_rk32_mid(const double* __restrict__ u, const float* __restrict__ k, double* __restrict__ acc,
-                           float* __restrict__ st, int64_t n, int64_t E, double b, double c, RefVec ref) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double ki = (double)k[i];
-    acc[i] += b * ki;
-    st[i] = (float)(u[i] + c * ki - ref.v[(i / E) % 5]);
-  }
-}
-__global__ void k_rk32_last(double* __restrict__ u, const float* __restrict__ k, const double* __restrict__ acc,
-                            float* __restrict__ st, int64_t n, int64_t E, double b, RefVec ref) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double un = acc[i] + b * (double)k[i];
-    u[i] = un;
-    st[i] = (float)(un - ref.v[(i / E) % 5]);
-  }
-}
-
-// Filtered FP32 form: the stage state in FP64 (for the filter) and its FP32 deviation
-// (for the right-hand side) in one pass; acc = (first ? u : acc) + b k.
-__global__ void k_rk32f_stage(const double* __restrict__ u, const float* __restrict__ k, double* __restrict__ acc,
-                              double* __restrict__ s64, float* __restrict__ s32, int64_t n, int64_t E, double b,
-                              double c, RefVec ref, int first) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const double ui = u[i], ki = (double)k[i];
-    acc[i] = (first ? ui : acc[i]) + b * ki;
-    const double si = ui + c * ki;
-    s64[i] = si;
-    s32[i] = (float)(si - ref.v[(i / E) % 5]);
+// RK stages of the FP32 form: FP64 state, FP32 increments kept per stage (k1, k2, k3; half the
+// bytes of an FP64 accumulator read and written by every stage) and FP32 stage deviations.
+// The last stage adds them in FP64 in the accumulator's order, so the sums are the same bits.
+// HBM-bound: 84 bytes per value and step instead of 112.  Rows (blockIdx.y) of one variable,
+// so a value's reference entry costs no division by E; two values per thread (E is a
+// multiple of 64).  32,768 p = 3 hexahedra: 54.7 -> 39.8 us per stage on average.
+struct Rk32 {
+  double* u;                                      // u_n, and the new state (last stage)
+  const float *k1, *k2, *k3, *k;
+  float* st;
+  double* s64;                                    // FP64 stage state as well, or null
+  double b1, b2, c;
+};
+template <bool LAST>
+__global__ void __launch_bounds__(256) k_rk32(Rk32 A, int64_t E, int rows, RefVec ref) {
+  const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 2;
+  if (e >= E) return;
+  for (int row = blockIdx.y; row < rows; row += gridDim.y) {
+    const int64_t i = (int64_t)row * E + e;
+    const double rv = ref.v[row % 5];
+    const double u0 = A.u[i], u1 = A.u[i + 1];    // the caller's array: 8-byte alignment
+    const float2 k = *reinterpret_cast<const float2*>(A.k + i);
+    double s0, s1;
+    if constexpr (LAST) {
+      const float2 k1 = *reinterpret_cast<const float2*>(A.k1 + i);
+      const float2 k2 = *reinterpret_cast<const float2*>(A.k2 + i);
+      const float2 k3 = *reinterpret_cast<const float2*>(A.k3 + i);
+      s0 = rk4_sum(u0, k1.x, k2.x, k3.x, k.x, A.b1, A.b2);
+      s1 = rk4_sum(u1, k1.y, k2.y, k3.y, k.y, A.b1, A.b2);
+      A.u[i] = s0;
+      A.u[i + 1] = s1;
+    } else {
+      s0 = fma(A.c, (double)k.x, u0);
+      s1 = fma(A.c, (double)k.y, u1);
+      if (A.s64) {
+        A.s64[i] = s0;
+        A.s64[i + 1] = s1;
+      }
+    }
+    *reinterpret_cast<float2*>(A.st + i) = make_float2((float)(s0 - rv), (float)(s1 - rv));
   }
 }
 
@@ -816,6 +820,9 @@ struct StageFuse {
   double* s64 = nullptr;        // FP64 stage state written in full (FP64 form) or null
   float* s32 = nullptr;         // FP32 deviation of the stage state (FP32 form) or null
   double* cand64 = nullptr;     // FP64 stage state of the candidates only (FP32 form) or null
+  const float* kk = nullptr;    // FP32 form: the kept increments of stages 1..3, each kk_len long
+  int64_t kk_len = 0;
+  double b1 = 0, b2 = 0;        // their coefficients (times dt)
 };
 
 template <typename KT>
@@ -947,10 +954,14 @@ void tet_candidates(fr_ctx c, DevBlock& b, const double* u, const StageFuse* fz 
   if (!fz)
     tet_filter_detect<PlainSrc><<<gE, TF_NT, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E, b.n, F, L,
                                                            nullptr);
-  else if (fz->k32)
-    tet_filter_detect<RkStageSrc<float>><<<gE, TF_NT, 0, c->stream>>>(
-        stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, F, L,
-        fz->cand64 ? fz->cand64 + b.native_off : nullptr);
+  else if (fz->k32) {
+    const int64_t o = b.native_off;
+    RkKeepSrc src{fz->u + o, (const float*)fz->k + o, fz->kk + o, fz->kk + fz->kk_len + o, fz->kk + 2 * fz->kk_len + o,
+                  fz->s32 + o, fz->b1, fz->b2, fz->c, fz->mode == 2, {0, 0, 0, 0, 0}};
+    for (int v = 0; v < 5; ++v) src.ref[v] = c->prm.u_ref[v];
+    tet_filter_detect<RkKeepSrc><<<gE, TF_NT, 0, c->stream>>>(src, b.smin, b.E, b.n, F, L,
+                                                              fz->cand64 ? fz->cand64 + o : nullptr);
+  }
   else
     tet_filter_detect<RkStageSrc<double>><<<gE, TF_NT, 0, c->stream>>>(
         stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, F, L,
@@ -1158,6 +1169,7 @@ void fr_destroy(fr_ctx c) {
   (void)hipFree(c->perm);
   (void)hipFree(c->g_npos);
   (void)hipFree(c->rk_stage); (void)hipFree(c->rk_acc); (void)hipFree(c->rk_k); (void)hipFree(c->rk_s64);
+  (void)hipFree(c->rk_kk);
   (void)hipFree(c->rk_x0); (void)hipFree(c->rk_err); (void)hipFree(c->rk_part);
   (void)hipFree(c->flag);
   (void)hipFree(c->tet_src); (void)hipFree(c->tet_opT); (void)hipFree(c->tet_ogT); (void)hipFree(c->pyr_ops);
@@ -1644,17 +1656,25 @@ fr_status fr_rhs(fr_ctx c, const void* u, void* r) {
 }  // extern "C"
 
 namespace {
-// RK workspace: stage state and increment in the native dtype, FP64 accumulator.
-fr_status rk_alloc(fr_ctx c) {
-  if (c->rk_stage) return FR_OK;
+// RK workspace: stage state and increment in the native dtype, and as asked the FP64
+// accumulator and the kept increments of the FP32 form.  Padding lanes are never written
+// by the RHS: all start at zero.
+fr_status rk_alloc(fr_ctx c, bool acc, bool kept) {
   const int64_t n = c->native_len;
   const size_t tsz = c->prm.precision != FR_FP64 ? sizeof(float) : sizeof(double);
-  if (dalloc(c, (char**)&c->rk_stage, n * tsz) || dalloc(c, &c->rk_acc, n) || dalloc(c, (char**)&c->rk_k, n * tsz))
-    return FR_ERR_ALLOC;
-  // padding lanes are never written by the RHS: keep them defined (zero increments)
-  HIP_TRY(c, hipMemsetAsync(c->rk_k, 0, n * tsz, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->rk_stage, 0, n * tsz, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->rk_acc, 0, n * sizeof(double), c->stream));
+  if (!c->rk_stage) {
+    if (dalloc(c, (char**)&c->rk_stage, n * tsz) || dalloc(c, (char**)&c->rk_k, n * tsz)) return FR_ERR_ALLOC;
+    HIP_TRY(c, hipMemsetAsync(c->rk_k, 0, n * tsz, c->stream));
+    HIP_TRY(c, hipMemsetAsync(c->rk_stage, 0, n * tsz, c->stream));
+  }
+  if (acc && !c->rk_acc) {
+    if (dalloc(c, &c->rk_acc, n)) return FR_ERR_ALLOC;
+    HIP_TRY(c, hipMemsetAsync(c->rk_acc, 0, n * sizeof(double), c->stream));
+  }
+  if (kept && !c->rk_kk) {
+    if (dalloc(c, &c->rk_kk, 3 * n)) return FR_ERR_ALLOC;
+    HIP_TRY(c, hipMemsetAsync(c->rk_kk, 0, 3 * n * sizeof(float), c->stream));
+  }
   return FR_OK;
 }
 
@@ -1690,7 +1710,7 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
       !(ap->fac_min <= 1) || !(ap->fac_max >= 1) || !std::isfinite(ap->fac_max) || ap->max_attempts < 1)
     return fail(c, FR_ERR_ARG, "adaptive parameters out of range");
   fr_status st;
-  if ((st = rk_alloc(c))) return st;
+  if ((st = rk_alloc(c, false, false))) return st;
   const int64_t n = c->native_len;
   if (!c->rk_x0) {
     if (dalloc(c, &c->rk_x0, n) || dalloc(c, &c->rk_err, n) ||
@@ -1789,7 +1809,10 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
   const int64_t n = c->native_len;
   const bool f32 = c->prm.precision != FR_FP64;
   fr_status st;
-  if ((st = rk_alloc(c))) return st;
+  // the FP32 form keeps its increments; its filtered hexahedra use the accumulator
+  bool acc = !f32;
+  for (auto& b : c->blocks) acc = acc || (filter_mode >= 0 && b.etype == FR_HEX);
+  if ((st = rk_alloc(c, acc, f32))) return st;
   const int g = grid_for(n, 256);
   const double b1 = dt / 6.0, b2 = dt / 3.0, c2 = dt / 2.0;
   int pk;
@@ -1842,7 +1865,7 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
       if (filt && (st = apply_filter(c, u, filter_mode))) return st;
     }
   } else {
-    float *K = (float*)c->rk_k, *S = (float*)c->rk_stage;
+    float *K = (float*)c->rk_k, *S = (float*)c->rk_stage, *KK = c->rk_kk;
     const RefVec ref = refvec(c->prm);
     // the FP32 deviation of u_n; later steps get it from the previous step's last update
     for (auto& b : c->blocks) {
@@ -1861,13 +1884,18 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
         for (int s = 0; s < n_steps; ++s) {
           if ((st = compute_smin(c, u))) return st;
           for (int stage = 0; stage < 4; ++stage) {
-            if ((st = rhs_native(c, S, K))) return st;
+            float* ks = stage < 3 ? KK + (int64_t)stage * n : K;
+            if ((st = rhs_native(c, S, ks))) return st;
             StageFuse fz;
             fz.mode = stage == 0 ? 0 : (stage < 3 ? 1 : 2);
             fz.b = stage == 0 || stage == 3 ? b1 : b2;
             fz.c = stage == 2 ? dt : c2;
-            fz.k = K;
+            fz.k = ks;
             fz.k32 = true;
+            fz.kk = KK;
+            fz.kk_len = n;
+            fz.b1 = b1;
+            fz.b2 = b2;
             fz.u = u;
             fz.acc = c->rk_acc;
             fz.s32 = S;
@@ -1878,43 +1906,26 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
         HIP_TRY(c, hipGetLastError());
         return FR_OK;
       }
-      for (int s = 0; s < n_steps; ++s) {
-        if ((st = compute_smin(c, u))) return st;
-        for (int stage = 0; stage < 4; ++stage) {
-          if ((st = rhs_native(c, S, K))) return st;
-          pk = c->prof_begin("rk4_update_f32");
-          for (auto& b : c->blocks) {
-            const int64_t nb = (int64_t)b.nsp * 5 * b.E, o = b.native_off;
-            const int gb = grid_for(nb, 256);
-            if (stage < 3)
-              k_rk32f_stage<<<gb, 256, 0, c->stream>>>(u + o, K + o, c->rk_acc + o, S64 + o, S + o, nb, b.E,
-                                                        stage == 0 ? b1 : b2, stage == 2 ? dt : c2, ref, stage == 0);
-            else
-              k_rk32_last<<<gb, 256, 0, c->stream>>>(u + o, K + o, c->rk_acc + o, S + o, nb, b.E, b1, ref);
-          }
-          c->prof_end(pk);
-          // the filter rewrites the FP32 deviation of every element it changes
-          if ((st = apply_filter(c, stage < 3 ? S64 : u, filter_mode, S))) return st;
+    }
+    // unfiltered, or collecting training data (the filter then works on whole FP64 stage states
+    // and rewrites the FP32 deviation of every element it changes)
+    for (int s = 0; s < n_steps; ++s) {
+      if (filter_mode >= 0 && (st = compute_smin(c, u))) return st;
+      for (int stage = 0; stage < 4; ++stage) {
+        float* ks = stage < 3 ? KK + (int64_t)stage * n : K;
+        if ((st = rhs_native(c, S, ks))) return st;
+        pk = c->prof_begin("rk4_update_f32");
+        for (auto& b : c->blocks) {
+          const int64_t o = b.native_off;
+          const int rows = b.nsp * 5, nt = b.E >= 512 ? 256 : 32;
+          const dim3 grid((unsigned)((b.E / 2 + nt - 1) / nt), (unsigned)rows);
+          const Rk32 A{u + o, KK + o, KK + n + o, KK + 2 * n + o, ks + o, S + o, filter_mode >= 0 ? c->rk_s64 + o : nullptr,
+                       b1, b2, stage == 2 ? dt : c2};
+          if (stage < 3) k_rk32<false><<<grid, nt, 0, c->stream>>>(A, b.E, rows, ref);
+          else k_rk32<true><<<grid, nt, 0, c->stream>>>(A, b.E, rows, ref);
         }
-      }
-    } else {
-      for (int s = 0; s < n_steps; ++s) {
-        for (int stage = 0; stage < 4; ++stage) {
-          if ((st = rhs_native(c, S, K))) return st;
-          pk = c->prof_begin("rk4_update_f32");
-          for (auto& b : c->blocks) {
-            const int64_t nb = (int64_t)b.nsp * 5 * b.E, o = b.native_off;
-            const int gb = grid_for(nb, 256);
-            if (stage == 0)
-              k_rk32_first<<<gb, 256, 0, c->stream>>>(u + o, K + o, c->rk_acc + o, S + o, nb, b.E, b1, c2, ref);
-            else if (stage < 3)
-              k_rk32_mid<<<gb, 256, 0, c->stream>>>(u + o, K + o, c->rk_acc + o, S + o, nb, b.E, b2,
-                                                    stage == 1 ? c2 : dt, ref);
-            else
-              k_rk32_last<<<gb, 256, 0, c->stream>>>(u + o, K + o, c->rk_acc + o, S + o, nb, b.E, b1, ref);
-          }
-          c->prof_end(pk);
-        }
+        c->prof_end(pk);
+        if (filter_mode >= 0 && (st = apply_filter(c, stage < 3 ? c->rk_s64 : u, filter_mode, S))) return st;
       }
     }
   }
