@@ -473,6 +473,10 @@ template <> struct HexCfg<1> { static constexpr int NE = 64; };
 template <> struct HexCfg<2> { static constexpr int NE = 32; };
 template <> struct HexCfg<3> { static constexpr int NE = 16; };
 template <> struct HexCfg<4> { static constexpr int NE = 8; };
+// element tile of the Euler divergence with the directions side by side (its LDS holds 15
+// values per point and element)
+template <typename T, int P>
+struct DivEulCfg { static constexpr int NE = P == 1 ? 32 : (P == 2 ? 16 : (P == 3 || sizeof(T) == 4 ? 8 : 4)); };
 // element tile of the NS divergence (its LDS holds 10 or 15 values per point and element)
 template <typename T, int P>
 struct DivNsCfg { static constexpr int NE = (sizeof(T) == 8 ? 8 : 16) / (P == 4 ? 2 : 1) * (P <= 2 ? 2 : 1); };
@@ -522,8 +526,17 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   const unsigned nblk = (unsigned)(b.E / NE);
   if (p.system == FR_EULER) {
     pk = c->prof_begin(("hex_div_euler" + sfx).c_str());
-    hex_div_euler<T, DEV, P, NE, CUR><<<nblk, NT, 0, c->stream>>>(u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma,
-                                                                   p.riemann, R);
+    // Directions side by side while every block has a CU of its own.  FP64, in turn / side by
+    // side, event-timed: 12^3 p = 3 (216 blocks) 16.9 / 13.9 us, 14^3 (352) 17.9 / 23.8; p = 2
+    // 16^3 (256) 21.4 / 13.1, 24^3 (864) 40.9 / 41.8; p = 4 10^3 (256) 19.9 / 16.9, 12^3 (432)
+    // 21.2 / 29.7; p = 1 20^3 (250) 14.7 / 11.2, 24^3 (432) 14.8 / 19.0.
+    constexpr int NEe = DivEulCfg<T, P>::NE;
+    if (b.E / NEe <= 256)
+      hex_div_euler_wide<T, DEV, P, NEe, CUR><<<(unsigned)(b.E / NEe), 3 * NEe * N1 * N1, 0, c->stream>>>(
+          u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma, p.riemann, R);
+    else
+      hex_div_euler<T, DEV, P, NE, CUR><<<nblk, NT, 0, c->stream>>>(u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma,
+                                                                     p.riemann, R);
     c->prof_end(pk);
   } else {
     pk = c->prof_begin(("hex_grad" + sfx).c_str());

@@ -494,6 +494,125 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_euler(
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same steps with a thread per line of each direction, for meshes of few blocks, where
+// the time is one block's latency: the three directions of an element run side by side, their
+// loads are all issued first and they meet in LDS once.  The LDS of three directions allows
+// half the elements per block, so it is slower as soon as the blocks queue.  Sums in
+// hex_div_euler's order.  Event-timed, FP64, in turn -> here: 4^3 p = 2 20.9 -> 11.8 us,
+// 12^3 p = 3 16.9 -> 13.9, 16^3 p = 2 21.4 -> 13.1.
+template <typename T, bool DEV, int P, int NE, bool CUR = false>
+__global__ void __launch_bounds__(3 * NE * (P + 1) * (P + 1)) hex_div_euler_wide(
+    const T* __restrict__ u, const T* __restrict__ uf, const T* __restrict__ geo, const T* __restrict__ cm,
+    Conn C, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, int riemann, RefState<T> R) {
+  constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = 3 * NE * NF;
+  __shared__ T DIV[3 * 5 * NSP * NE];              // [d][v][pt][el]
+  __shared__ T G[CUR ? 1 : 24 * NE];
+  const int el = threadIdx.x % NE, dl = threadIdx.x / NE, d = dl / NF, l = dl % NF;
+  const int64_t e0 = xcd_block() * NE, e = e0 + el;
+  const int t0 = l % N1, t1 = l / N1;
+  const NbrSlot ns0 = nbr_slot<NF>(C, E, e, 2 * d, l), ns1 = nbr_slot<NF>(C, E, e, 2 * d + 1, l);
+  T uu[N1][5], un[2][5];
+#pragma unroll
+  for (int a = 0; a < N1; ++a)
+#pragma unroll
+    for (int v = 0; v < 5; ++v) uu[a][v] = u[((int64_t)line_pt<N1>(d, a, t0, t1) * 5 + v) * E + e];
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    un[0][v] = uf[((int64_t)ns0.fp * 5 + v) * E + ns0.elem];
+    un[1][v] = uf[((int64_t)ns1.fp * 5 + v) * E + ns1.elem];
+  }
+  if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
+  __syncthreads();
+  const T gm1 = gamma - T(1);
+  // row d of S at reference point xi (straight elements)
+  auto metric = [&](const T xi[3], T s[3]) {
+    T g[3][3], p[3], q[3];
+    hex_cols(G + el, NE, xi[0], xi[1], xi[2], g);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      p[k] = d == 0 ? g[1][k] : (d == 1 ? g[2][k] : g[0][k]);
+      q[k] = d == 0 ? g[2][k] : (d == 1 ? g[0][k] : g[1][k]);
+    }
+    cross3(p, q, s);
+  };
+  T ft[5][N1], tm[5] = {0, 0, 0, 0, 0}, tp[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+  for (int a = 0; a < N1; ++a) {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      tm[v] += K.lm[a] * uu[a][v];
+      tp[v] += K.lp[a] * uu[a][v];
+    }
+    T s[3], f[5], vs, pr;
+    if constexpr (CUR) {
+      cm_srow<T, NSP>(cm, E, e, line_pt<N1>(d, a, t0, t1), d, s);
+    } else {
+      T xi[3];
+      line_xi(K, d, a, t0, t1, xi);
+      metric(xi, s);
+    }
+    Flux<T, DEV>::eval(uu[a], s[0], s[1], s[2], gm1, R, f, vs, pr);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) ft[v][a] = f[v];
+  }
+  T Fc[2][5];
+#pragma unroll
+  for (int sd = 0; sd < 2; ++sd) {
+    T nv[3];
+    if constexpr (CUR) {
+      cm_fnrm<T, NSP>(cm, E, e, (2 * d + sd) * NF + l, nv);
+    } else {
+      T xi[3];
+      end_xi(K, d, sd, t0, t1, xi);
+      metric(xi, nv);
+    }
+    const T sg = sd ? T(1) : T(-1);
+    const T mag = fsqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
+    const bool left = sd ? ns1.left : ns0.left;
+    const T* own = sd ? tp : tm;
+    T uL[5], uR[5], nL[3], F[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) { uL[v] = left ? own[v] : un[sd][v]; uR[v] = left ? un[sd][v] : own[v]; }
+    const T sl = fdiv(left ? sg : -sg, mag);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) nL[k] = nv[k] * sl;
+    common_inviscid<T, DEV>(riemann, uL, uR, nL, gamma, R, F);
+    const T fs = left ? mag : -mag;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) Fc[sd][v] = fs * F[v];
+  }
+#pragma unroll
+  for (int a = 0; a < N1; ++a) {
+    T* D = DIV + (d * 5 * NSP + line_pt<N1>(d, a, t0, t1)) * NE + el;
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      T acc = K.cp[a] * Fc[1][v] + K.cm[a] * Fc[0][v];
+#pragma unroll
+      for (int b = 0; b < N1; ++b) acc += K.Dh[a][b] * ft[v][b];
+      D[v * NSP * NE] = acc;
+    }
+  }
+  __syncthreads();
+  if (e >= n) return;
+  // a point per thread: the three directions' sum
+  for (int pt = dl; pt < NSP; pt += 3 * NF) {
+    T iJ;
+    if constexpr (CUR) {
+      iJ = -cm_rjac<T, NSP>(cm, E, e, pt);
+    } else {
+      T g[3][3];
+      hex_cols(G + el, NE, K.x[pt % N1], K.x[pt / N1 % N1], K.x[pt / (N1 * N1)], g);
+      iJ = -rcp(det_cols(g));
+    }
+    const T* D = DIV + pt * NE + el;
+#pragma unroll
+    for (int v = 0; v < 5; ++v)
+      r[((int64_t)pt * 5 + v) * E + e] =
+          (D[v * NSP * NE] + D[(5 + v) * NSP * NE] + D[(10 + v) * NSP * NE]) * iJ;
+  }
+}
+
 // LDS slot of point pt in the gradient kernel's [component][point][element] buffer.
 // With 4 points per line and 16 FP32 elements a point row is 16 banks, and the rows
 // a wave touches on a line along xi_1 are 4 apart (same 16 banks of 64): the XOR of
