@@ -115,8 +115,8 @@ def kernel_bytes_per_elem(name, nsp, nfp):
     per tetrahedron (the affine map), connectivity 2 int32 per face.  NS uses the
     one-sided LDG switch (beta = 1/2): the gradient kernel reads the neighbour's
     solution trace only on faces where the element is the right side and stores
-    gradient traces only there (half of the flux points); the face kernel reads one
-    gradient trace per flux point pair, i.e. the stored half.  Curved hexahedra ("_cur")
+    f_v.n (4 words) only there (half of the flux points), beside the viscous flux of
+    each solution point (9 words); the face kernel reads the stored half.  Curved hexahedra ("_cur")
     read stored metric terms instead of the 24 corner words: S rows and 1/J at the
     solution points (10 words each) where a kernel forms fluxes or gradients there,
     row d of S at the flux points (3 words each) where it forms common fluxes (the
@@ -144,7 +144,8 @@ def kernel_bytes_per_elem(name, nsp, nfp):
         if plain is None:
             return None
         metric = {"hex_trace": 0, "hex_div_euler": 10 * nsp + 3 * nfp, "hex_grad": 10 * nsp,
-                  "hex_face_ns": 3 * nfp // 2, "hex_div_ns": 10 * nsp}.get(base)
+                  "hex_face_ns": 3 * nfp // 2, "hex_div_ns": 10 * nsp, "hex_grad_vf": 10 * nsp + 3 * nfp // 2,
+                  "hex_face_vf": 3 * nfp // 2, "hex_div_vf": 10 * nsp}.get(base)
         geo = 0 if base == "hex_trace" else 24 * d
         return None if metric is None else plain - geo + d * metric
     hex_geo, hex_conn = 24 * d, 6 * 2 * 4
@@ -153,6 +154,10 @@ def kernel_bytes_per_elem(name, nsp, nfp):
     table = {
         "hex_trace": d * 5 * (nsp + nfp),
         "hex_div_euler": d * (5 * nsp + 5 * nfp + 5 * nsp) + hex_geo + hex_conn,
+        "hex_grad_vf": d * (5 * nsp + 5 * nfp // 2 + 9 * nsp + 4 * nfp // 2) + hex_geo + hex_conn,
+        "hex_face_vf": d * (5 * nfp + 4 * nfp // 2 + 5 * nfp) + hex_geo + hex_conn,
+        "hex_div_vf": d * (5 * nsp + 9 * nsp + 5 * nfp + 5 * nsp) + hex_geo,
+        # the same steps with the gradient and its traces stored (15 words each)
         "hex_grad": d * (5 * nsp + 5 * nfp // 2 + 15 * nsp + 15 * nfp // 2) + hex_geo + hex_conn,
         "hex_face_ns": d * (5 * nfp + 15 * nfp // 2 + 5 * nfp) + hex_geo + hex_conn,
         "hex_div_ns": d * (5 * nsp + 15 * nsp + 5 * nfp + 5 * nsp) + hex_geo,

@@ -51,8 +51,8 @@ struct DevBlock {
   int32_t* nbr_elem = nullptr;
   int32_t* nbr_info = nullptr;
   void* uf = nullptr;       // [nfp][5][E]
-  void* grad = nullptr;     // [nsp][15][E]
-  void* gradf = nullptr;    // [nfp][15][E]
+  void* grad = nullptr;     // [nsp][15][E]; hexahedra: the points' viscous flux, [nsp][9][E]
+  void* gradf = nullptr;    // [nfp][15][E]; hexahedra: f_v.n, [nfp][4][E]
   void* fc = nullptr;       // [nfp][5][E] common fluxes (Navier--Stokes)
   void* cmet = nullptr;     // curved hexahedra: stored metric terms in the kernels' type (else NULL)
   int64_t elem_off = 0;     // offset of the block in the element numbering (both orders)
@@ -477,6 +477,16 @@ template <> struct HexCfg<4> { static constexpr int NE = 8; };
 // values per point and element)
 template <typename T, int P>
 struct DivEulCfg { static constexpr int NE = P == 1 ? 32 : (P == 2 ? 16 : (P == 3 || sizeof(T) == 4 ? 8 : 4)); };
+// Element tile of the NS gradient and the threads per column of an element (its LDS holds 15
+// values per point and element).  28^3 p = 4 FP64, us: 8 elements and 2 threads 223, 4 and 5
+// 251, 8 and 3 436 (over the registers of its 10 waves); 32^3 p = 3 FP64: 2 threads 147, 4 173,
+// 1 191; FP32 28^3 p = 4: 8 and 5 113, 8 and 2 141, 16 and 2 142; 32^3 p = 3: 16 elements and
+// 2 threads 73, 4 threads 75, 8 elements 78; 40^3 p = 2: 3 threads 76, 1 118.
+template <typename T, int P>
+struct HexGradCfg {
+  static constexpr int NE = P == 4 ? 8 : (sizeof(T) == 8 ? 1 : 2) * (P == 1 ? 32 : (P == 2 ? 16 : 8));
+  static constexpr int KT = P == 1 ? 2 : (P == 2 ? 3 : (P == 3 || sizeof(T) == 8 ? 2 : 5));
+};
 // element tile of the NS divergence (its LDS holds 10 or 15 values per point and element)
 template <typename T, int P>
 struct DivNsCfg { static constexpr int NE = (sizeof(T) == 8 ? 8 : 16) / (P == 4 ? 2 : 1) * (P <= 2 ? 2 : 1); };
@@ -539,32 +549,26 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
                                                                      p.riemann, R);
     c->prof_end(pk);
   } else {
-    pk = c->prof_begin(("hex_grad" + sfx).c_str());
-    if constexpr (P <= 3)
-      hex_grad<T, P, NE, CUR><<<nblk, NT, 0, c->stream>>>(u, uf, geo, cm, C, grad, gradf, b.E, K, (T)p.ldg_beta, sm);
-    else {
-      // 16 FP32 elements per tile (64-byte rows); FP64 keeps 8 (64-byte rows as well)
-      constexpr int NEg = sizeof(T) == 4 ? 16 : NE;
-      hex_grad_lines<T, P, NEg, CUR><<<(unsigned)(b.E / NEg), NEg * N1 * N1, 0, c->stream>>>(
-          u, uf, geo, cm, C, grad, gradf, b.E, K, (T)p.ldg_beta, sm);
-    }
+    pk = c->prof_begin(("hex_grad_vf" + sfx).c_str());
+    using GC = HexGradCfg<T, P>;
+    hex_grad<T, DEV, P, GC::NE, GC::KT, CUR><<<(unsigned)(b.E / GC::NE), GC::NE * N1 * N1 * GC::KT, 0, c->stream>>>(
+        u, uf, geo, cm, C, grad, gradf, b.E, K, (T)p.gamma, (T)p.mu, (T)p.prandtl, (T)p.ldg_beta, sm, R);
     c->prof_end(pk);
     T* fc = (T*)b.fc;
     const int64_t face_threads = b.E * 6 * N1 * N1;
-    pk = c->prof_begin(("hex_face_ns" + sfx).c_str());
+    pk = c->prof_begin(("hex_face_vf" + sfx).c_str());
     hex_face_ns<T, DEV, P, CUR><<<(unsigned)((face_threads + 255) / 256), 256, 0, c->stream>>>(
-        uf, gradf, geo, cm, C, fc, b.E, b.n, K, (T)p.gamma, (T)p.mu, (T)p.prandtl, (T)p.ldg_beta, (T)p.ldg_tau,
-        p.riemann, sm, R);
+        uf, gradf, geo, cm, C, fc, b.E, b.n, K, (T)p.gamma, (T)p.ldg_beta, (T)p.ldg_tau, p.riemann, sm, R);
     c->prof_end(pk);
     constexpr int NE2 = DivNsCfg<T, P>::NE;
-    pk = c->prof_begin(("hex_div_ns" + sfx).c_str());
+    pk = c->prof_begin(("hex_div_vf" + sfx).c_str());
     // f~_3 of a column in registers except for FP64 at p = 4 (all of f~ in LDS there)
     if constexpr (P <= 3 || sizeof(T) == 4)
       hex_div_ns<T, DEV, P, NE2, CUR><<<(unsigned)(b.E / NE2), NE2 * N1 * N1, 0, c->stream>>>(
-          u, grad, fc, geo, cm, r, b.E, b.n, K, (T)p.gamma, (T)p.mu, (T)p.prandtl, R);
+          u, grad, fc, geo, cm, r, b.E, b.n, K, (T)p.gamma, R);
     else
       hex_div_ns_lds<T, DEV, P, NE2, CUR><<<(unsigned)(b.E / NE2), NE2 * N1 * N1, 0, c->stream>>>(
-          u, grad, fc, geo, cm, r, b.E, b.n, K, (T)p.gamma, (T)p.mu, (T)p.prandtl, R);
+          u, grad, fc, geo, cm, r, b.E, b.n, K, (T)p.gamma, R);
     c->prof_end(pk);
   }
   hipError_t e = hipGetLastError();
@@ -1275,10 +1279,10 @@ fr_status setup_impl(const fr_params* p, int64_t n_vert, const double* xyz, cons
     if (dalloc(c, &d.geo, hb.geo.size()) || dalloc(c, &d.nbr_elem, hb.nbr_elem.size()) ||
         dalloc(c, &d.nbr_info, hb.nbr_info.size()) || dalloc(c, (char**)&d.uf, (size_t)d.nfp * 5 * d.E * tsz))
       return bail(FR_ERR_ALLOC);
-    const bool is_tet = d.etype == FR_TET;
+    const bool is_tet = d.etype == FR_TET, is_hex = d.etype == FR_HEX;
     if (p->system == FR_NAVIER_STOKES &&
-        (dalloc(c, (char**)&d.grad, (size_t)d.nsp * 15 * d.E * tsz) ||
-         (!is_tet && dalloc(c, (char**)&d.gradf, (size_t)d.nfp * 15 * d.E * tsz))))
+        (dalloc(c, (char**)&d.grad, (size_t)d.nsp * (is_hex ? 9 : 15) * d.E * tsz) ||
+         (!is_tet && dalloc(c, (char**)&d.gradf, (size_t)d.nfp * (is_hex ? 4 : 15) * d.E * tsz))))
       return bail(FR_ERR_ALLOC);
     if (p->system == FR_NAVIER_STOKES && dalloc(c, (char**)&d.fc, (size_t)d.nfp * 5 * d.E * tsz))
       return bail(FR_ERR_ALLOC);

@@ -215,6 +215,15 @@ struct PointFluxNS {
   }
 };
 
+// Stored viscous flux of a point (PointFluxNS's tau and qe, 9 values) along s, taken off f.
+template <typename T>
+__device__ __forceinline__ void minus_visc(const T q[9], T sx, T sy, T sz, T f[5]) {
+  f[1] -= q[0] * sx + q[3] * sy + q[4] * sz;
+  f[2] -= q[3] * sx + q[1] * sy + q[5] * sz;
+  f[3] -= q[4] * sx + q[5] * sy + q[2] * sz;
+  f[4] -= q[6] * sx + q[7] * sy + q[8] * sz;
+}
+
 // The inviscid part of PointFluxNS: f_inv.s along several directions of one point.
 template <typename T, bool DEV>
 struct PointInv {
@@ -613,11 +622,10 @@ __global__ void __launch_bounds__(3 * NE * (P + 1) * (P + 1)) hex_div_euler_wide
   }
 }
 
-// LDS slot of point pt in the gradient kernel's [component][point][element] buffer.
-// With 4 points per line and 16 FP32 elements a point row is 16 banks, and the rows
-// a wave touches on a line along xi_1 are 4 apart (same 16 banks of 64): the XOR of
-// the point's low two bits with the next two spreads the four rows of every line
-// direction over different bank groups.  A bijection on [0, 64).
+// LDS slot of point pt in the gradient kernel's [component][point][element] buffers.
+// With 4 points per line and rows of 64 bytes a point row is 16 banks, and the rows a wave
+// touches on lines along xi_1 are 4 apart (same 16 banks of 64): the XOR of the point's low
+// two bits with the next two spreads them over different bank groups.  A bijection on [0, 64).
 template <typename T, int N1, int NE>
 __device__ __forceinline__ int gr_slot(int pt) {
   if constexpr (N1 == 4 && NE * sizeof(T) == 64) return pt ^ ((pt >> 2) & 3);
@@ -625,271 +633,184 @@ __device__ __forceinline__ int gr_slot(int pt) {
 }
 
 // ---------------------------------------------------------------------------
-// Navier--Stokes phase 1: corrected gradient (LDG common solution u^ at the flux
-// points), physical gradient at the solution points, and its traces at the flux
-// points that the viscous common flux will read.  side_mode: +1 when beta = +1/2
-// (u^ = u_L, the viscous common flux takes the right side only: the left side's
-// jump vanishes and only right-side traces are stored), -1 for beta = -1/2 (the
-// mirror case), 0 in general.
-template <typename T, int P, int NE, bool CUR = false>
-__global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_grad(
+// Navier--Stokes phase 1: corrected gradient (LDG common solution u^ at the flux points),
+// and from it the viscous fluxes: the physical f_v of every solution point (tau and the
+// energy flux vector, 9 values where the gradient has 15) and f_v.n of the own trace and the
+// traced gradient at the flux points that the viscous common flux reads (4 values for 15; n
+// the left side's unit normal).  side_mode: +1 when beta = +1/2 (u^ = u_L, the viscous common
+// flux takes the right side only: the left side's jump vanishes and only right sides store
+// f_v.n), -1 for beta = -1/2 (the mirror case), 0 in general.
+//
+// Bound by its bytes (state, partner traces, 9 + up to 9 values per point out).  All the
+// global reads are issued first; the state goes to LDS, the line ends form u^ (own traces
+// stay in registers), each thread forms all 15 components of its points' gradients in
+// registers, and these replace the state in LDS for the traces: four barriers in all.
+// Bytes aside, its vector instructions (about 870 per FP32 point at p = 3) are what it pays:
+// addresses step from one base per array.  With the pass that follows it, against storing the
+// 15 gradient components and their traces and forming both fluxes later, us (gradient / common
+// flux / divergence): 32^3 p = 3 FP32 76 / 49 / 83 -> 73 / 34 / 51, FP64 158 / 120 / 146 ->
+// 147 / 74 / 125; 28^3 p = 4 FP64 232 / 123 / 278 -> 223 / 80 / 242; 10^3 p = 3 FP64 gradient
+// 21.6 -> 13.6.
+template <typename T, bool DEV, int P, int NE, int KT, bool CUR>
+__global__ void __launch_bounds__(NE*(P + 1)*(P + 1)*KT) hex_grad(
     const T* __restrict__ u, const T* __restrict__ uf, const T* __restrict__ geo, const T* __restrict__ cm,
-    Conn C, T* __restrict__ grad, T* __restrict__ gradf, int64_t E, HexK<T> K, T beta, int side_mode) {
-  constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = NE * N1 * N1;
-  __shared__ T GR[3 * NSP * NE];
-  __shared__ T U[5 * NSP * NE];       // the block's state, [pt*5 + v][el]
+    Conn C, T* __restrict__ vf, T* __restrict__ fvn, int64_t E, HexK<T> K, T gamma, T mu, T pr, T beta, int side_mode,
+    RefState<T> R) {
+  constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, W = NF * KT, NT = NE * W;
+  constexpr int PPT = (N1 + KT - 1) / KT, EPT = (6 * NF + W - 1) / W;
+  constexpr int ROWS = 15 * NSP > 5 * NSP + 30 * NF ? 15 * NSP : 5 * NSP + 30 * NF;
+  __shared__ T S[ROWS * NE];
   __shared__ T G[CUR ? 1 : 24 * NE];
-  const int el = threadIdx.x % NE, l = threadIdx.x / NE;
+  T* const U = S;                        // the block's state, [v][pt][el]; then the gradients, [c][pt][el]
+  T* const UH = S + 5 * NSP * NE;        // u^ at the line ends, [f][v][el]
+  const int el = threadIdx.x % NE, w = threadIdx.x / NE;
   const int64_t e0 = xcd_block() * NE, e = e0 + el;
-  const int t0 = l % N1, t1 = l / N1;
-  // the global reads up front: geometry, the block's state and the neighbour traces at
-  // this thread's 6 line ends (only where the common value is not the own trace)
+  auto at = [&](int c, int pt) -> int { return (c * NSP + gr_slot<T, N1, NE>(pt)) * NE + el; };
+  // ends f = w, w + W, ...: end f's line starts at point b0 with stride st
+  auto line_of = [&](int f, int& d, int& b0, int& st) {
+    const int q = f % NF;
+    d = f / (2 * NF);
+    b0 = d == 0 ? q * N1 : (d == 1 ? q % N1 + NF * (q / N1) : q);
+    st = d == 0 ? 1 : (d == 1 ? N1 : NF);
+  };
+  NbrSlot ns[EPT];
+  bool need[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int f = w + i * W < 6 * NF ? w + i * W : 0;
+    ns[i] = nbr_slot<NF>(C, E, e, f / NF, f % NF);
+    need[i] = side_mode == 0 || (side_mode > 0 ? !ns[i].left : ns[i].left);
+  }
   if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
-  for (int i = threadIdx.x; i < 5 * NSP * NE; i += NT) U[i] = u[(int64_t)(i / NE) * E + e0 + i % NE];
-  auto uval = [&](int pt, int v) -> T { return U[(pt * 5 + v) * NE + el]; };
-  T uh[3][2][5];
-  bool need[3][2], left[3][2];
+  // (one 64-bit address per thread and array, uniform steps from there: the 64-bit products of
+  // an address per load were a quarter of the kernel's issue slots)
+  const T* const uw = u + (int64_t)w * E + e;
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int i = 0; i < (5 * NSP + W - 1) / W; ++i) {
+    const int row = w + i * W;
+    if (row < 5 * NSP) U[at(row % 5, row / 5)] = uw[(int64_t)i * W * E];
+  }
+  T un[EPT][5], own[EPT][5];
 #pragma unroll
-    for (int sd = 0; sd < 2; ++sd) {
-      const NbrSlot s = nbr_slot<NF>(C, E, e, 2 * d + sd, l);
-      left[d][sd] = s.left;
-      need[d][sd] = side_mode == 0 || (side_mode > 0 ? !s.left : s.left);
+  for (int i = 0; i < EPT; ++i) {
+    const T* const un_i = uf + (int64_t)ns[i].fp * 5 * E + ns[i].elem;
 #pragma unroll
-      for (int v = 0; v < 5; ++v) uh[d][sd][v] = need[d][sd] ? uf[((int64_t)s.fp * 5 + v) * E + s.elem] : T(0);
-    }
+    for (int v = 0; v < 5; ++v) un[i][v] = need[i] ? un_i[(int64_t)v * E] : T(0);
+  }
   __syncthreads();
-  // metric of this thread's line points, once for all five variables: row d of S over J
-  T sJ[3][N1][3];
+  // common solution values u^ (LDG) at the line ends
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int a = 0; a < N1; ++a) {
-      T s[3], iJ;
-      if constexpr (CUR) {
-        const int pt = line_pt<N1>(d, a, t0, t1);
-        cm_srow<T, NSP>(cm, E, e, pt, d, s);
-        iJ = cm_rjac<T, NSP>(cm, E, e, pt);
-      } else {
-        T xi[3], g[3][3];
-        line_xi(K, d, a, t0, t1, xi);
-        hex_cols(G + el, NE, xi[0], xi[1], xi[2], g);
-        srow(g, d, s);
-        iJ = rcp(det_cols(g));
-      }
-#pragma unroll
-      for (int j = 0; j < 3; ++j) sJ[d][a][j] = s[j] * iJ;
-    }
-  // common solution values u^ (LDG) at the 6 line ends
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int i = 0; i < EPT; ++i) {
+    const int f = w + i * W;
+    if (f >= 6 * NF) break;
+    int d, b0, st;
+    line_of(f, d, b0, st);
+    const bool sd = (f / NF) & 1;
+    const T bs = ns[i].left ? beta : -beta;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      T tm = 0, tp = 0;
+      T x = 0;
 #pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        const T x = uval(line_pt<N1>(d, a, t0, t1), v);
-        tm += K.lm[a] * x;
-        tp += K.lp[a] * x;
-      }
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd) {
-        const T own = sd ? tp : tm, un = uh[d][sd][v];
-        const T uL = left[d][sd] ? own : un, uR = left[d][sd] ? un : own;
-        uh[d][sd][v] = need[d][sd] ? T(0.5) * (uL + uR) + beta * (uL - uR) : own;
-      }
+      for (int a = 0; a < N1; ++a) x += (sd ? K.lp[a] : K.lm[a]) * U[at(v, b0 + a * st)];
+      own[i][v] = x;
+      UH[(f * 5 + v) * NE + el] = need[i] ? T(0.5) * (x + un[i][v]) + bs * (x - un[i][v]) : x;
     }
-#pragma unroll
-  for (int v = 0; v < 5; ++v) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T uv[N1];
-#pragma unroll
-      for (int a = 0; a < N1; ++a) uv[a] = uval(line_pt<N1>(d, a, t0, t1), v);
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        T gt = K.cp[a] * uh[d][1][v] - K.cm[a] * uh[d][0][v];
-#pragma unroll
-        for (int b = 0; b < N1; ++b) gt += K.Dh[a][b] * uv[b];
-        const int pt = line_pt<N1>(d, a, t0, t1);
-        T* Gp = GR + (gr_slot<T, N1, NE>(pt) * NE + el);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          if (d == 0) Gp[j * NSP * NE] = sJ[d][a][j] * gt;
-          else Gp[j * NSP * NE] += sJ[d][a][j] * gt;
-        }
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int a = 0; a < N1; ++a) {
-      const int pt = line_pt<N1>(2, a, t0, t1);
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-        grad[((int64_t)pt * 15 + v * 3 + j) * E + e] = GR[(j * NSP + gr_slot<T, N1, NE>(pt)) * NE + el];
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T gm[3] = {0, 0, 0}, gp[3] = {0, 0, 0};
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        const int pt = line_pt<N1>(d, a, t0, t1);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const T val = GR[(j * NSP + gr_slot<T, N1, NE>(pt)) * NE + el];
-          gm[j] += K.lm[a] * val;
-          gp[j] += K.lp[a] * val;
-        }
-      }
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd) {
-        // stored only where a neighbour will read it
-        const bool keep = side_mode == 0 || (side_mode > 0 ? !left[d][sd] : left[d][sd]);
-        if (!keep) continue;
-        const int f = (2 * d + sd) * NF + l;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) gradf[((int64_t)f * 15 + v * 3 + j) * E + e] = sd ? gp[j] : gm[j];
-      }
-    }
-    __syncthreads();
   }
-}
-
-// Variant for p = 4: the state is read from global memory (L2) per line and variable
-// instead of being staged, which keeps the LDS and registers of the 125-point element
-// within an occupancy of 3-4 waves per SIMD.
-template <typename T, int P, int NE, bool CUR = false>
-__global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 1))) hex_grad_lines(
-    const T* __restrict__ u, const T* __restrict__ uf, const T* __restrict__ geo, const T* __restrict__ cm,
-    Conn C, T* __restrict__ grad, T* __restrict__ gradf, int64_t E, HexK<T> K, T beta, int side_mode) {
-  constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = NE * N1 * N1;
-  // the physical gradient's contributions of the three line directions, one slot per
-  // direction ([d][j][pt][el]): every value has one writer, so the three directions of a
-  // variable run without a barrier between them, and the output phase adds the slots
-  __shared__ T GR[9 * NSP * NE];
-  __shared__ T G[CUR ? 1 : 24 * NE];
-  const int el = threadIdx.x % NE, l = threadIdx.x / NE;
-  const int64_t e0 = xcd_block() * NE, e = e0 + el;
-  const int t0 = l % N1, t1 = l / N1;
-  if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
-  // connectivity of this thread's 6 line ends
-  NbrSlot ns[3][2];
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd) ns[d][sd] = nbr_slot<NF>(C, E, e, 2 * d + sd, l);
   __syncthreads();
-  // metric of this thread's line points, once for all five variables: row d of S over J
-  T sJ[3][N1][3];
+  // all 15 components at the points (ci, cj, k0 + m KT), and their viscous flux
+  const int c2 = w % NF, ci = c2 % N1, cj = c2 / N1, k0 = w / NF;
+  T g[PPT][15];
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int m = 0; m < PPT; ++m) {
+    const int k = k0 + m * KT;
+    if (k >= N1) break;
+    const int pt = c2 + NF * k;
+    T sJ[3][3];
+    if constexpr (CUR) {
+      const T iJ = cm_rjac<T, NSP>(cm, E, e, pt);
 #pragma unroll
-    for (int a = 0; a < N1; ++a) {
-      T s[3], iJ;
-      if constexpr (CUR) {
-        const int pt = line_pt<N1>(d, a, t0, t1);
-        cm_srow<T, NSP>(cm, E, e, pt, d, s);
-        iJ = cm_rjac<T, NSP>(cm, E, e, pt);
-      } else {
-        T xi[3], g[3][3];
-        line_xi(K, d, a, t0, t1, xi);
-        hex_cols(G + el, NE, xi[0], xi[1], xi[2], g);
-        srow(g, d, s);
-        iJ = rcp(det_cols(g));
+      for (int d = 0; d < 3; ++d) {
+        cm_srow<T, NSP>(cm, E, e, pt, d, sJ[d]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) sJ[d][j] *= iJ;
       }
+    } else {
+      T gc[3][3];
+      hex_cols(G + el, NE, K.x[ci], K.x[cj], K.x[k], gc);
+      const T iJ = rcp(det_cols(gc));
 #pragma unroll
-      for (int j = 0; j < 3; ++j) sJ[d][a][j] = s[j] * iJ;
-    }
-  // the line values (and the partner traces the common value needs) of the next
-  // (variable, direction) are loaded before the current one is worked on, so the loads
-  // of one step overlap the arithmetic and the barrier of the previous one
-  bool need[3][2];
+      for (int d = 0; d < 3; ++d) {
+        srow(gc, d, sJ[d]);
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd)
-      // the common value equals the own trace when the switch points at this side
-      need[d][sd] = side_mode == 0 || (side_mode > 0 ? !ns[d][sd].left : ns[d][sd].left);
-  T nuv[N1], nun[2];
-  auto load_line = [&](int v, int d) {
-#pragma unroll
-    for (int a = 0; a < N1; ++a) nuv[a] = u[((int64_t)line_pt<N1>(d, a, t0, t1) * 5 + v) * E + e];
-#pragma unroll
-    for (int sd = 0; sd < 2; ++sd)
-      nun[sd] = need[d][sd] ? uf[((int64_t)ns[d][sd].fp * 5 + v) * E + ns[d][sd].elem] : T(0);
-  };
-  load_line(0, 0);
-  for (int v = 0; v < 5; ++v) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T uv[N1], unb[2], tm = 0, tp = 0;
-#pragma unroll
-      for (int a = 0; a < N1; ++a) uv[a] = nuv[a];
-      unb[0] = nun[0];
-      unb[1] = nun[1];
-      if (d < 2) load_line(v, d + 1);
-      else if (v < 4) load_line(v + 1, 0);
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        tm += K.lm[a] * uv[a];
-        tp += K.lp[a] * uv[a];
-      }
-      T uh[2];
-#pragma unroll
-      for (int sd = 0; sd < 2; ++sd) {
-        const NbrSlot& s = ns[d][sd];
-        const T own = sd ? tp : tm;
-        const T un = need[d][sd] ? unb[sd] : own;
-        const T uL = s.left ? own : un, uR = s.left ? un : own;
-        uh[sd] = need[d][sd] ? T(0.5) * (uL + uR) + beta * (uL - uR) : own;
-      }
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        T gt = K.cp[a] * uh[1] - K.cm[a] * uh[0];
-#pragma unroll
-        for (int b = 0; b < N1; ++b) gt += K.Dh[a][b] * uv[b];
-        const int pt = line_pt<N1>(d, a, t0, t1);
-        T* Gp = GR + d * 3 * NSP * NE + (gr_slot<T, N1, NE>(pt) * NE + el);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) Gp[j * NSP * NE] = sJ[d][a][j] * gt;
+        for (int j = 0; j < 3; ++j) sJ[d][j] *= iJ;
       }
     }
-    __syncthreads();
-    auto gsum = [&](int j, int pt) {
-      const int o = (j * NSP + gr_slot<T, N1, NE>(pt)) * NE + el;
-      return (GR[o] + GR[3 * NSP * NE + o]) + GR[6 * NSP * NE + o];
-    };
+    const int q0 = cj + N1 * k, q1 = NF * 2 + ci + N1 * k, q2 = NF * 4 + c2;
 #pragma unroll
-    for (int a = 0; a < N1; ++a) {
-      const int pt = line_pt<N1>(2, a, t0, t1);
+    for (int v = 0; v < 5; ++v) {
+      T gt[3];
+      gt[0] = K.cp[ci] * UH[((q0 + NF) * 5 + v) * NE + el] - K.cm[ci] * UH[(q0 * 5 + v) * NE + el];
+      gt[1] = K.cp[cj] * UH[((q1 + NF) * 5 + v) * NE + el] - K.cm[cj] * UH[(q1 * 5 + v) * NE + el];
+      gt[2] = K.cp[k] * UH[((q2 + NF) * 5 + v) * NE + el] - K.cm[k] * UH[(q2 * 5 + v) * NE + el];
 #pragma unroll
-      for (int j = 0; j < 3; ++j)
-        grad[((int64_t)pt * 15 + v * 3 + j) * E + e] = gsum(j, pt);
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      T gm[3] = {0, 0, 0}, gp[3] = {0, 0, 0};
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        const int pt = line_pt<N1>(d, a, t0, t1);
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          const T val = gsum(j, pt);
-          gm[j] += K.lm[a] * val;
-          gp[j] += K.lp[a] * val;
-        }
+      for (int b = 0; b < N1; ++b) {
+        gt[0] += K.Dh[ci][b] * U[at(v, b + N1 * (cj + N1 * k))];
+        gt[1] += K.Dh[cj][b] * U[at(v, ci + N1 * (b + N1 * k))];
+        gt[2] += K.Dh[k][b] * U[at(v, c2 + NF * b)];
       }
 #pragma unroll
-      for (int sd = 0; sd < 2; ++sd) {
-        // stored only where a neighbour will read it
-        if (!need[d][sd]) continue;
-        const int f = (2 * d + sd) * NF + l;
-#pragma unroll
-        for (int j = 0; j < 3; ++j) gradf[((int64_t)f * 15 + v * 3 + j) * E + e] = sd ? gp[j] : gm[j];
-      }
+      for (int j = 0; j < 3; ++j) g[m][v * 3 + j] = sJ[0][j] * gt[0] + sJ[1][j] * gt[1] + sJ[2][j] * gt[2];
     }
-    __syncthreads();
+    T wv[5];
+#pragma unroll
+    for (int v = 0; v < 5; ++v) wv[v] = U[at(v, pt)];
+    const PointFluxNS<T, DEV> pf(wv, g[m], gamma, mu, pr, R);
+    T* const vp = vf + (int64_t)w * 9 * E + e;       // (pt = w + m * W)
+#pragma unroll
+    for (int q = 0; q < 9; ++q) vp[(int64_t)(m * W * 9 + q) * E] = q < 6 ? pf.tau[q < 6 ? q : 0] : pf.qe[q < 6 ? 0 : q - 6];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int m = 0; m < PPT; ++m) {
+    const int k = k0 + m * KT;
+    if (k >= N1) break;
+#pragma unroll
+    for (int c = 0; c < 15; ++c) S[at(c, c2 + NF * k)] = g[m][c];
+  }
+  __syncthreads();
+  T* const fw = fvn + (int64_t)w * 4 * E + e;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int f = w + i * W;
+    // stored only where the common flux will read it
+    if (f >= 6 * NF) break;
+    if (!need[i]) continue;
+    int d, b0, st;
+    line_of(f, d, b0, st);
+    const bool sd = (f / NF) & 1;
+    T gf[15], nv[3], fv[5];
+#pragma unroll
+    for (int c = 0; c < 15; ++c) {
+      T x = 0;
+#pragma unroll
+      for (int a = 0; a < N1; ++a) x += (sd ? K.lp[a] : K.lm[a]) * S[at(c, b0 + a * st)];
+      gf[c] = x;
+    }
+    if constexpr (CUR) {
+      cm_fnrm<T, NSP>(cm, E, e, f, nv);
+    } else {
+      T xi[3], gc[3][3];
+      end_xi(K, d, sd, f % N1, f % NF / N1, xi);
+      hex_cols(G + el, NE, xi[0], xi[1], xi[2], gc);
+      if (d == 0) srow(gc, 0, nv);
+      else if (d == 1) srow(gc, 1, nv);
+      else srow(gc, 2, nv);
+    }
+    const T mag = fsqrt(nv[0] * nv[0] + nv[1] * nv[1] + nv[2] * nv[2]);
+    const T sl = fdiv(sd == ns[i].left ? T(1) : T(-1), mag);
+    viscous<T, DEV>(own[i], gf, nv[0] * sl, nv[1] * sl, nv[2] * sl, gamma, mu, pr, R, fv);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) fw[(int64_t)(i * W * 4 + v) * E] = fv[v + 1];
   }
 }
 
@@ -900,12 +821,12 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) __attribute__((amdgpu_wave
 // lanes over elements; the left side of each pair computes it once and writes
 // +|S^T n~| times it into its own slot and the negative into the right side's slot
 // (conservative by construction).  With a one-sided switch only the contributing
-// side's gradient trace is read (stored by hex_grad in that side's slot).
+// side's f_v.n is read (stored by hex_grad in that side's slot).
 template <typename T, bool DEV, int P, bool CUR = false>
-__global__ void __launch_bounds__(256) hex_face_ns(const T* __restrict__ uf, const T* __restrict__ gradf,
+__global__ void __launch_bounds__(256) hex_face_ns(const T* __restrict__ uf, const T* __restrict__ fvn,
                                                    const T* __restrict__ geo, const T* __restrict__ cm, Conn C,
                                                    T* __restrict__ fc, int64_t E,
-                                                   int64_t n, HexK<T> K, T gamma, T mu, T pr, T beta, T tau,
+                                                   int64_t n, HexK<T> K, T gamma, T beta, T tau,
                                                    int riemann, int side_mode, RefState<T> R) {
   constexpr int N1 = P + 1, NF = N1 * N1, NFP = 6 * NF, NSP = N1 * N1 * N1;
   const int64_t gtid = xcd_block() * 256 + threadIdx.x;
@@ -956,12 +877,8 @@ __global__ void __launch_bounds__(256) hex_face_ns(const T* __restrict__ uf, con
     if (side_mode != 0 && wgt == T(0)) continue;
     const int64_t gs = side == 0 ? (int64_t)fp : (int64_t)ns.fp;
     const int64_t ge = side == 0 ? e : ns.elem;
-    T gk[15], fv[5];
 #pragma unroll
-    for (int k = 0; k < 15; ++k) gk[k] = gradf[(gs * 15 + k) * E + ge];
-    viscous<T, DEV>(side == 0 ? own : un, gk, nL[0], nL[1], nL[2], gamma, mu, pr, R, fv);
-#pragma unroll
-    for (int v = 0; v < 5; ++v) fvc[v] += wgt * fv[v];
+    for (int v = 0; v < 4; ++v) fvc[v + 1] += wgt * fvn[(gs * 4 + v) * E + ge];
   }
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
@@ -980,8 +897,8 @@ __global__ void __launch_bounds__(256) hex_face_ns(const T* __restrict__ uf, con
 // line contractions through that point from LDS.
 template <typename T, bool DEV, int P, int NE, bool CUR = false>
 __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
-    const T* __restrict__ u, const T* __restrict__ grad, const T* __restrict__ fc, const T* __restrict__ geo,
-    const T* __restrict__ cm, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, T mu, T pr, RefState<T> R) {
+    const T* __restrict__ u, const T* __restrict__ vf, const T* __restrict__ fc, const T* __restrict__ geo,
+    const T* __restrict__ cm, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, RefState<T> R) {
   constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = NE * N1 * N1;
   // f~ along xi_1 and xi_2 go through LDS ([d][v][pt][el]); along xi_3 the line is the
   // thread's own column, so f~_3 and its common fluxes stay in registers
@@ -993,16 +910,17 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
   if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
   __syncthreads();
   const T gm1 = gamma - T(1);
+  T* const rl = r + (int64_t)l * 5 * E + e;
   T iJ[N1], f3[N1][5];
   // the state and gradient of the column's next point are loaded while the current
   // point's fluxes are formed (two buffers), so a wave keeps loads in flight
-  T ub[2][5], gb[2][15];
+  T ub[2][5], gb[2][9];
+  const T *const ul = u + (int64_t)l * 5 * E + e, *const vl = vf + (int64_t)l * 9 * E + e;
   auto load_pt = [&](int k, T* uu, T* gg) {
-    const int pt = ci + N1 * (cj + N1 * k);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) uu[v] = u[((int64_t)pt * 5 + v) * E + e];
+    for (int v = 0; v < 5; ++v) uu[v] = ul[(int64_t)(k * NF * 5 + v) * E];
 #pragma unroll
-    for (int q = 0; q < 15; ++q) gg[q] = grad[((int64_t)pt * 15 + q) * E + e];
+    for (int q = 0; q < 9; ++q) gg[q] = vl[(int64_t)(k * NF * 9 + q) * E];
   };
   load_pt(0, ub[0], gb[0]);
 #pragma unroll
@@ -1018,13 +936,14 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
       hex_cols(G + el, NE, K.x[ci], K.x[cj], K.x[k], g);
       iJ[k] = -rcp(det_cols(g));
     }
-    const PointFluxNS<T, DEV> pf(uu, gg, gamma, mu, pr, R);
+    const PointInv<T, DEV> pf(uu, gamma, R);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       T s[3], f[5];
       if constexpr (CUR) cm_srow<T, NSP>(cm, E, e, pt, d, s);
       else srow(g, d, s);
       pf.dir(s[0], s[1], s[2], f);
+      minus_visc(gg, s[0], s[1], s[2], f);
 #pragma unroll
       for (int v = 0; v < 5; ++v) {
         if (d < 2) FT[((d * 5 + v) * NSP + pt) * NE + el] = f[v];
@@ -1043,14 +962,15 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
   // common fluxes at the xi_1 and xi_2 ends of the lines through point k, all five
   // variables at once; the next point's are loaded while the current one is summed
   T fb[2][4][5];
+  const T *const f0 = fc + (int64_t)cj * 5 * E + e, *const f1 = fc + (int64_t)ci * 5 * E + e;
   auto load_ends = [&](int k, T (&F)[4][5]) {
-    const int q0 = cj + N1 * k, q1 = ci + N1 * k;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      F[0][v] = fc[(((int64_t)0 * NF + q0) * 5 + v) * E + e];
-      F[1][v] = fc[(((int64_t)1 * NF + q0) * 5 + v) * E + e];
-      F[2][v] = fc[(((int64_t)2 * NF + q1) * 5 + v) * E + e];
-      F[3][v] = fc[(((int64_t)3 * NF + q1) * 5 + v) * E + e];
+      const int64_t o = (int64_t)(N1 * k * 5 + v) * E;
+      F[0][v] = f0[o];
+      F[1][v] = f0[(int64_t)NF * 5 * E + o];
+      F[2][v] = f1[(int64_t)NF * 10 * E + o];
+      F[3][v] = f1[(int64_t)NF * 15 * E + o];
     }
   };
   load_ends(0, fb[0]);
@@ -1073,7 +993,7 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
       }
       acc += K.cp[a0] * F[1][v] + K.cm[a0] * F[0][v];
       acc += K.cp[a1] * F[3][v] + K.cm[a1] * F[2][v];
-      if (e < n) r[((int64_t)pt * 5 + v) * E + e] = acc * iJ[k];
+      if (e < n) rl[(int64_t)(k * NF * 5 + v) * E] = acc * iJ[k];
     }
   }
 }
@@ -1085,8 +1005,8 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
 // fourth block spills and is slower.)
 template <typename T, bool DEV, int P, int NE, bool CUR = false>
 __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
-    const T* __restrict__ u, const T* __restrict__ grad, const T* __restrict__ fc, const T* __restrict__ geo,
-    const T* __restrict__ cm, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, T mu, T pr, RefState<T> R) {
+    const T* __restrict__ u, const T* __restrict__ vf, const T* __restrict__ fc, const T* __restrict__ geo,
+    const T* __restrict__ cm, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, RefState<T> R) {
   constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = NE * N1 * N1;
   __shared__ T FT[3 * 5 * NSP * NE];       // [d][v][pt][el]
   __shared__ T G[CUR ? 1 : 24 * NE];
@@ -1096,17 +1016,18 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
   if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
   __syncthreads();
   const T gm1 = gamma - T(1);
+  T* const rl = r + (int64_t)l * 5 * E + e;
   T iJ[N1];
   // as in hex_div_ns: the next point's state and gradient load while the current
   // point's fluxes are formed (this variant is held to 1-2 waves per SIMD by its LDS,
   // so registers are not what limits it)
-  T ub[2][5], gb[2][15];
+  T ub[2][5], gb[2][9];
+  const T *const ul = u + (int64_t)l * 5 * E + e, *const vl = vf + (int64_t)l * 9 * E + e;
   auto load_pt = [&](int k, T* uu, T* gg) {
-    const int pt = ci + N1 * (cj + N1 * k);
 #pragma unroll
-    for (int v = 0; v < 5; ++v) uu[v] = u[((int64_t)pt * 5 + v) * E + e];
+    for (int v = 0; v < 5; ++v) uu[v] = ul[(int64_t)(k * NF * 5 + v) * E];
 #pragma unroll
-    for (int q = 0; q < 15; ++q) gg[q] = grad[((int64_t)pt * 15 + q) * E + e];
+    for (int q = 0; q < 9; ++q) gg[q] = vl[(int64_t)(k * NF * 9 + q) * E];
   };
   load_pt(0, ub[0], gb[0]);
 #pragma unroll
@@ -1122,13 +1043,14 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
       hex_cols(G + el, NE, K.x[ci], K.x[cj], K.x[k], g);
       iJ[k] = -rcp(det_cols(g));
     }
-    const PointFluxNS<T, DEV> pf(uu, gg, gamma, mu, pr, R);
+    const PointInv<T, DEV> pf(uu, gamma, R);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       T s[3], f[5];
       if constexpr (CUR) cm_srow<T, NSP>(cm, E, e, pt, d, s);
       else srow(g, d, s);
       pf.dir(s[0], s[1], s[2], f);
+      minus_visc(gg, s[0], s[1], s[2], f);
 #pragma unroll
       for (int v = 0; v < 5; ++v) FT[((d * 5 + v) * NSP + pt) * NE + el] = f[v];
     }
@@ -1142,14 +1064,15 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
     F4[v] = fc[(((int64_t)4 * NF + q2) * 5 + v) * E + e];
     F5[v] = fc[(((int64_t)5 * NF + q2) * 5 + v) * E + e];
   }
+  const T *const f0 = fc + (int64_t)cj * 5 * E + e, *const f1 = fc + (int64_t)ci * 5 * E + e;
   auto load_ends = [&](int k, T (&F)[4][5]) {
-    const int q0 = cj + N1 * k, q1 = ci + N1 * k;
 #pragma unroll
     for (int v = 0; v < 5; ++v) {
-      F[0][v] = fc[(((int64_t)0 * NF + q0) * 5 + v) * E + e];
-      F[1][v] = fc[(((int64_t)1 * NF + q0) * 5 + v) * E + e];
-      F[2][v] = fc[(((int64_t)2 * NF + q1) * 5 + v) * E + e];
-      F[3][v] = fc[(((int64_t)3 * NF + q1) * 5 + v) * E + e];
+      const int64_t o = (int64_t)(N1 * k * 5 + v) * E;
+      F[0][v] = f0[o];
+      F[1][v] = f0[(int64_t)NF * 5 * E + o];
+      F[2][v] = f1[(int64_t)NF * 10 * E + o];
+      F[3][v] = f1[(int64_t)NF * 15 * E + o];
     }
   };
   load_ends(0, fb[0]);
@@ -1173,7 +1096,7 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
       acc += K.cp[a0] * F[1][v] + K.cm[a0] * F[0][v];
       acc += K.cp[a1] * F[3][v] + K.cm[a1] * F[2][v];
       acc += K.cp[a2] * F5[v] + K.cm[a2] * F4[v];
-      if (e < n) r[((int64_t)pt * 5 + v) * E + e] = acc * iJ[k];
+      if (e < n) rl[(int64_t)(k * NF * 5 + v) * E] = acc * iJ[k];
     }
   }
 }
