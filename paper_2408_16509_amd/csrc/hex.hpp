@@ -1,8 +1,8 @@
 // Hexahedral FR kernels (order P, Gauss--Legendre points).
 //
 // Native layout: state u[(pt*5 + v)*E + e] (element fastest, E = padded count),
-// traces uf[(fp*5 + v)*E + e], gradients grad[(pt*15 + v*3 + j)*E + e] and
-// gradf[(fp*15 + v*3 + j)*E + e].  Solution point pt = i + N1*(j + N1*k); flux point
+// traces uf[(fp*5 + v)*E + e], viscous fluxes vf[(pt*9 + q)*E + e] (tau, energy flux) and
+// fvn[(fp*4 + v)*E + e] (f_v.n).  Solution point pt = i + N1*(j + N1*k); flux point
 // fp = face*N1^2 + q, face = 2*d + (xi_d > 0), q = t0 + N1*t1 over the two tangential
 // axes of the face in increasing order.
 //
