@@ -557,9 +557,14 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   const int64_t trace_threads = b.E * 3 * N1 * N1;
   static const std::string sfx =
       std::string(CUR ? "_cur" : "") + (sizeof(T) == 8 ? "" : "_f32") + "_p" + std::to_string(P);
-  int pk = c->prof_begin(("hex_trace" + sfx).c_str());
-  hex_trace<T, P><<<(unsigned)((trace_threads + 255) / 256), 256, 0, c->stream>>>(u, uf, b.E, K);
-  c->prof_end(pk);
+  constexpr int NEe = DivEulCfg<T, P>::NE;
+  const bool wide = p.system == FR_EULER && b.E / NEe <= 256;
+  int pk = 0;
+  if (!wide || !wide_own_traces<T, P>()) {
+    pk = c->prof_begin(("hex_trace" + sfx).c_str());
+    hex_trace<T, P><<<(unsigned)((trace_threads + 255) / 256), 256, 0, c->stream>>>(u, uf, b.E, K);
+    c->prof_end(pk);
+  }
   const unsigned nblk = (unsigned)(b.E / NE);
   if (p.system == FR_EULER) {
     pk = c->prof_begin(("hex_div_euler" + sfx).c_str());
@@ -567,8 +572,7 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
     // side, event-timed: 12^3 p = 3 (216 blocks) 16.9 / 13.9 us, 14^3 (352) 17.9 / 23.8; p = 2
     // 16^3 (256) 21.4 / 13.1, 24^3 (864) 40.9 / 41.8; p = 4 10^3 (256) 19.9 / 16.9, 12^3 (432)
     // 21.2 / 29.7; p = 1 20^3 (250) 14.7 / 11.2, 24^3 (432) 14.8 / 19.0.
-    constexpr int NEe = DivEulCfg<T, P>::NE;
-    if (b.E / NEe <= 256)
+    if (wide)
       hex_div_euler_wide<T, DEV, P, NEe, CUR><<<(unsigned)(b.E / NEe), 3 * NEe * N1 * N1, 0, c->stream>>>(
           u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma, p.riemann, R);
     else

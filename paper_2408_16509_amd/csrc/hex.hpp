@@ -510,30 +510,64 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_euler(
 // half the elements per block, so it is slower as soon as the blocks queue.  Sums in
 // hex_div_euler's order.  Event-timed, FP64, in turn -> here: 4^3 p = 2 20.9 -> 11.8 us,
 // 12^3 p = 3 16.9 -> 13.9, 16^3 p = 2 21.4 -> 13.1.
+// wide_own_traces: the partners' traces are formed here from their lines and hex_trace is not
+// launched.  Both kernels -> this one, FP64: 4^3 p = 2 18.3 -> 13.0 us, 10^3 p = 3 20.6 -> 18.3;
+// not in FP64 at p = 4, where the lines do not fit the registers (10^3 24 -> 32; FP32 21 -> 18).
+template <typename T, int P>
+constexpr bool wide_own_traces() { return P < 4 || sizeof(T) == 4; }
 template <typename T, bool DEV, int P, int NE, bool CUR = false>
 __global__ void __launch_bounds__(3 * NE * (P + 1) * (P + 1)) hex_div_euler_wide(
     const T* __restrict__ u, const T* __restrict__ uf, const T* __restrict__ geo, const T* __restrict__ cm,
     Conn C, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, int riemann, RefState<T> R) {
   constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = 3 * NE * NF;
+  constexpr bool LN = wide_own_traces<T, P>();
   __shared__ T DIV[3 * 5 * NSP * NE];              // [d][v][pt][el]
   __shared__ T G[CUR ? 1 : 24 * NE];
   const int el = threadIdx.x % NE, dl = threadIdx.x / NE, d = dl / NF, l = dl % NF;
   const int64_t e0 = xcd_block() * NE, e = e0 + el;
   const int t0 = l % N1, t1 = l / N1;
   const NbrSlot ns0 = nbr_slot<NF>(C, E, e, 2 * d, l), ns1 = nbr_slot<NF>(C, E, e, 2 * d + 1, l);
-  T uu[N1][5], un[2][5];
+  T uu[N1][5], ub[LN ? 2 : 1][LN ? N1 : 1][5], un[2][5];
 #pragma unroll
   for (int a = 0; a < N1; ++a)
 #pragma unroll
     for (int v = 0; v < 5; ++v) uu[a][v] = u[((int64_t)line_pt<N1>(d, a, t0, t1) * 5 + v) * E + e];
+  // the partners' lines: point b0 + a st of the face's line
+  auto load_nbr = [&](const NbrSlot& ns, int sd) {
+    const int dn = ns.fp / (2 * NF), q = ns.fp % NF;
+    const int b0 = dn == 0 ? q * N1 : (dn == 1 ? q % N1 + NF * (q / N1) : q), st = dn == 0 ? 1 : (dn == 1 ? N1 : NF);
+    const T* const p = u + (int64_t)b0 * 5 * E + ns.elem;
 #pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    un[0][v] = uf[((int64_t)ns0.fp * 5 + v) * E + ns0.elem];
-    un[1][v] = uf[((int64_t)ns1.fp * 5 + v) * E + ns1.elem];
+    for (int a = 0; a < N1; ++a)
+#pragma unroll
+      for (int v = 0; v < 5; ++v) ub[sd][a][v] = p[((int64_t)a * st * 5 + v) * E];
+  };
+  if constexpr (LN) {
+    load_nbr(ns0, 0);
+    load_nbr(ns1, 1);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      un[0][v] = uf[((int64_t)ns0.fp * 5 + v) * E + ns0.elem];
+      un[1][v] = uf[((int64_t)ns1.fp * 5 + v) * E + ns1.elem];
+    }
   }
   if constexpr (!CUR) stage_geo<T, NE, NT>(geo, E, e0, G);
   __syncthreads();
   const T gm1 = gamma - T(1);
+  if constexpr (LN) {
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+      const bool top = ((sd ? ns1.fp : ns0.fp) / NF) & 1;
+#pragma unroll
+      for (int v = 0; v < 5; ++v) {
+        T x = 0;
+#pragma unroll
+        for (int a = 0; a < N1; ++a) x += (top ? K.lp[a] : K.lm[a]) * ub[sd][a][v];
+        un[sd][v] = x;
+      }
+    }
+  }
   // row d of S at reference point xi (straight elements)
   auto metric = [&](const T xi[3], T s[3]) {
     T g[3][3], p[3], q[3];
