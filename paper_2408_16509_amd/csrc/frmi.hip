@@ -560,7 +560,7 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   constexpr int NEe = DivEulCfg<T, P>::NE;
   const bool wide = p.system == FR_EULER && b.E / NEe <= 256;
   int pk = 0;
-  if (!wide || !wide_own_traces<T, P>()) {
+  if (!wide || !wide_own_traces<T, P, CUR>()) {
     pk = c->prof_begin(("hex_trace" + sfx).c_str());
     hex_trace<T, P><<<(unsigned)((trace_threads + 255) / 256), 256, 0, c->stream>>>(u, uf, b.E, K);
     c->prof_end(pk);

@@ -507,20 +507,22 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_euler(
 // The same steps with a thread per line of each direction, for meshes of few blocks, where
 // the time is one block's latency: the three directions of an element run side by side, their
 // loads are all issued first and they meet in LDS once.  The LDS of three directions allows
-// half the elements per block, so it is slower as soon as the blocks queue.  Sums in
-// hex_div_euler's order.  Event-timed, FP64, in turn -> here: 4^3 p = 2 20.9 -> 11.8 us,
-// 12^3 p = 3 16.9 -> 13.9, 16^3 p = 2 21.4 -> 13.1.
+// half the elements per block.  Sums in hex_div_euler's order.
 // wide_own_traces: the partners' traces are formed here from their lines and hex_trace is not
-// launched.  Both kernels -> this one, FP64: 4^3 p = 2 18.3 -> 13.0 us, 10^3 p = 3 20.6 -> 18.3;
-// not in FP64 at p = 4, where the lines do not fit the registers (10^3 24 -> 32; FP32 21 -> 18).
-template <typename T, int P>
-constexpr bool wide_own_traces() { return P < 4 || sizeof(T) == 4; }
+// launched, where both lines of a thread fit beside the rest of its registers and cost little
+// more than the traces when the partners lie scattered.  A whole right-hand side of 2,030
+// renumbered elements, us, by hex_trace and hex_div_euler / by hex_trace and this / with the
+// lines: p = 3 FP64 straight 23.0 / 20.1 / 23.6, curved 21.1 / 16.6 / 15.4; FP32 straight
+// 16.8 / 14.7 / 13.5, curved 14.6 / 12.2 / 10.9; p = 4 FP32 straight 20.8 / 20.7 / 24.2, curved
+// 18.7 / 17.6 / 20.0 (p = 4 FP64, 10^3 in order: 24 with the traces, 32 with the lines).
+template <typename T, int P, bool CUR>
+constexpr bool wide_own_traces() { return P < 3 || (P == 3 && (CUR || sizeof(T) == 4)); }
 template <typename T, bool DEV, int P, int NE, bool CUR = false>
 __global__ void __launch_bounds__(3 * NE * (P + 1) * (P + 1)) hex_div_euler_wide(
     const T* __restrict__ u, const T* __restrict__ uf, const T* __restrict__ geo, const T* __restrict__ cm,
     Conn C, T* __restrict__ r, int64_t E, int64_t n, HexK<T> K, T gamma, int riemann, RefState<T> R) {
   constexpr int N1 = P + 1, NSP = N1 * N1 * N1, NF = N1 * N1, NT = 3 * NE * NF;
-  constexpr bool LN = wide_own_traces<T, P>();
+  constexpr bool LN = wide_own_traces<T, P, CUR>();
   __shared__ T DIV[3 * 5 * NSP * NE];              // [d][v][pt][el]
   __shared__ T G[CUR ? 1 : 24 * NE];
   const int el = threadIdx.x % NE, dl = threadIdx.x / NE, d = dl / NF, l = dl % NF;
