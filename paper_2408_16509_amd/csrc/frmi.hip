@@ -504,6 +504,24 @@ template <> struct HexCfg<4> { static constexpr int NE = 8; };
 // values per point and element)
 template <typename T, int P>
 struct DivEulCfg { static constexpr int NE = P == 1 ? 32 : (P == 2 ? 16 : (P == 3 || sizeof(T) == 4 ? 8 : 4)); };
+// Most blocks for which the Euler divergence takes its directions side by side.  A whole
+// right-hand side (with hex_trace where a form launches it) in turn / side by side, over meshes in
+// order, of ragged sides and renumbered, straight and curved (the range over the three):
+//   p = 3, p = 4 (all forms): 1.01-1.72 to 256 blocks (every block has a CU of its own),
+//     0.50-1.13 from 288 on;
+//   p = 1 FP64 straight: 1.54-1.93 to 256, 0.96-1.22 to 768, 0.73-0.96 from 896;
+//   p = 2 FP32 straight: 1.63-1.78 to 256, 0.98-1.10 to 512, 0.63-0.92 from 640;
+//   p = 1 FP32 straight: 1.17-1.57 to 768, 0.92-1.02 at 1,024, 0.72-0.90 from 1,536;
+//   p = 2 FP64 straight: 1.02-1.38 to 768, 0.95-1.24 above (renumbered meshes lose);
+//   p = 2 FP32 curved: 1.15-1.42 to 768, 0.94-1.18 above (renumbered meshes lose);
+//   p = 1 curved: 1.00-2.15, p = 2 FP64 curved: 1.15-2.32, to 8,192 blocks, the largest timed.
+constexpr int64_t kAnyBlocks = INT64_MAX;
+template <typename T, int P, bool CUR>
+constexpr int64_t wide_blocks() {
+  if (CUR && (P == 1 || (P == 2 && sizeof(T) == 8))) return kAnyBlocks;
+  if ((P == 1 && sizeof(T) == 4) || (P == 2 && (CUR || sizeof(T) == 8))) return 768;
+  return 256;
+}
 // Element tile of the NS gradient and the threads per column of an element (its LDS holds 15
 // values per point and element).  28^3 p = 4 FP64, us: 8 elements and 2 threads 223, 4 and 5
 // 251, 8 and 3 436 (over the registers of its 10 waves); 32^3 p = 3 FP64: 2 threads 147, 4 173,
@@ -558,7 +576,8 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   static const std::string sfx =
       std::string(CUR ? "_cur" : "") + (sizeof(T) == 8 ? "" : "_f32") + "_p" + std::to_string(P);
   constexpr int NEe = DivEulCfg<T, P>::NE;
-  const bool wide = p.system == FR_EULER && b.E / NEe <= 256;
+  constexpr int64_t wide_most = wide_blocks<T, P, CUR>();
+  const bool wide = p.system == FR_EULER && b.E / NEe <= wide_most;
   int pk = 0;
   if (!wide || !wide_own_traces<T, P, CUR>()) {
     pk = c->prof_begin(("hex_trace" + sfx).c_str());
@@ -568,14 +587,10 @@ fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   const unsigned nblk = (unsigned)(b.E / NE);
   if (p.system == FR_EULER) {
     pk = c->prof_begin(("hex_div_euler" + sfx).c_str());
-    // Directions side by side while every block has a CU of its own.  FP64, in turn / side by
-    // side, event-timed: 12^3 p = 3 (216 blocks) 16.9 / 13.9 us, 14^3 (352) 17.9 / 23.8; p = 2
-    // 16^3 (256) 21.4 / 13.1, 24^3 (864) 40.9 / 41.8; p = 4 10^3 (256) 19.9 / 16.9, 12^3 (432)
-    // 21.2 / 29.7; p = 1 20^3 (250) 14.7 / 11.2, 24^3 (432) 14.8 / 19.0.
     if (wide)
       hex_div_euler_wide<T, DEV, P, NEe, CUR><<<(unsigned)(b.E / NEe), 3 * NEe * N1 * N1, 0, c->stream>>>(
           u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma, p.riemann, R);
-    else
+    else if constexpr (wide_most < kAnyBlocks)
       hex_div_euler<T, DEV, P, NE, CUR><<<nblk, NT, 0, c->stream>>>(u, uf, geo, cm, C, r, b.E, b.n, K, (T)p.gamma,
                                                                      p.riemann, R);
     c->prof_end(pk);

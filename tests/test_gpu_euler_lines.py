@@ -1,7 +1,8 @@
-"""The Euler divergence with its directions side by side, the forms whose partners' traces come
-from hex_trace on curved p = 4 elements: below and past the mesh size at which the other form
-takes over.  Copies of a small curved box; every copy has to give the oracle's residual, FP64
-1e-12 and FP32 1e-5 of well-conditioned states as in the other element tests."""
+"""The Euler divergence with its directions side by side: the forms whose partners' traces come
+from hex_trace on curved p = 4 elements, below and past the mesh size at which the other form
+takes over, and the forms whose line lies elsewhere.  Copies of a small box; every copy has to
+give the oracle's residual, FP64 1e-12 and FP32 1e-5 of well-conditioned states as in the other
+element tests."""
 import numpy as np
 import pytest
 
@@ -37,3 +38,16 @@ def test_curved_p4_either_side_of_the_line(fp32, riemann):
     mesh = inputs.curved_hex_box((5, 3, 1), q=2, amp=0.1)
     below = 256 * (8 if fp32 else 4) // 15
     _check(mesh, 4, riemann, frmi.FR_FP32 if fp32 else frmi.FR_FP64, 1e-5 if fp32 else 1e-12, (1, below, below + 5))
+
+
+@pytest.mark.parametrize("order,curved,fp32,blocks", [(1, False, True, 768), (2, False, False, 768), (2, True, True, 768),
+                                                      (1, True, False, 300), (1, True, True, 300), (2, True, False, 800)])
+def test_lines_past_one_block_per_cu(order, curved, fp32, blocks):
+    """The forms that run side by side on larger meshes: at their line, just past it (or past
+    256 blocks, where there is no line)."""
+    from paper_2408_16509_amd import frmi
+    n = (5, 13, 1)
+    mesh = inputs.curved_hex_box(n, q=order, amp=0.1) if curved else inputs.hex_box(n, perturb=0.1, perturb_seed=3,
+                                                                                    permute_seed=4)
+    at = blocks * (32 if order == 1 else 16) // 65
+    _check(mesh, order, 1, frmi.FR_FP32 if fp32 else frmi.FR_FP64, 1e-5 if fp32 else 1e-12, (at, at + 1))
