@@ -224,7 +224,7 @@ constexpr int TET_KA16 = 112, TET_KB16 = 64, TET_KP16 = TET_KA16 + TET_KB16;
 // five waves of which two only gather); in FP32 a fourth wave joins the gathers and the
 // flux evaluation (four blocks per CU either way, set by LDS: 1.286 -> 1.246 ms).  The
 // gradient gathers more (the common solution at all 60 flux points): four waves (three
-// multiply; FP32 2.95 -> 2.47 ms per launch against five).
+// multiply; FP32 2.95 -> 2.47 ms per launch against five), five in two-sided FP64.
 constexpr int TDIV_NE = 16;
 // Layout of the transformed viscous fluxes S_i . f_v that the one-sided gradient kernel stores
 // for the divergence kernel (12 rows per solution point): tile by tile of NE elements,
@@ -245,7 +245,14 @@ __device__ __forceinline__ int64_t tet_fc_index(int64_t e, int row) {
 }
 template <typename T>
 constexpr int tdiv_nt() { return sizeof(T) == 4 ? 4 * 64 : 3 * 64; }
-constexpr int TGR_NT = 4 * 64;
+// the gradient: the two-sided FP64 form (curved elements always take it) five waves at four
+// waves per SIMD, the one-sided FP64 form four at two, as its registers need.  A right-hand
+// side of FP64 curved tetrahedra, us, by five / four waves: 144 elements 38.6 / 39.7, 3,072
+// 47.4 / 48.1, 24,576 212 / 218
+template <typename T, bool FC>
+constexpr int tgr_nt() { return sizeof(T) == 8 && !FC ? 5 * 64 : 4 * 64; }
+template <typename T, bool FC>
+constexpr int tgr_wpe() { return sizeof(T) == 8 && FC ? 2 : 4; }
 
 // Corrected divergence (eq:FRfinal) on the matrix cores: per block of 16 elements,
 // R^T = -(1/J) Op P with the panel P = [f~_0; f~_1; f~_2; F^C] (K x 5*16).  A block
@@ -617,13 +624,13 @@ __device__ __forceinline__ void tet_grad_contract(typename Mma16<T>::V (&acc)[3]
 }
 
 template <typename T, bool DEV, bool BF3, bool FC, bool CUR = false>
-__global__ void __launch_bounds__(TGR_NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 4 : 2))) tet_grad_mma(const T* __restrict__ u, const T* __restrict__ geo, Conn C,
+__global__ void __launch_bounds__((tgr_nt<T, FC>())) __attribute__((amdgpu_waves_per_eu(tgr_wpe<T, FC>()))) tet_grad_mma(const T* __restrict__ u, const T* __restrict__ geo, Conn C,
                                                         TetDev<T> O, const T* __restrict__ ogT,
                                                         const tet_s4* __restrict__ ogH, const tet_s4* __restrict__ ogL,
                                                         T* __restrict__ grad, T* __restrict__ fc, int64_t E, int64_t n,
                                                         T beta, int side_mode, T gamma, T mu, T pr, T tau, int riemann,
                                                         RefState<T> R) {
-  constexpr int NE = TDIV_NE, NT = TGR_NT;
+  constexpr int NE = TDIV_NE, NT = tgr_nt<T, FC>();
   constexpr int KR = BF3 ? TGR_K : TGS_K;
   // [k][v][el]: u at the 35 points, u^ at the 60 flux points (BF16x3: rows 35..94; else
   // face by face, tgs_row), zero rows
