@@ -217,13 +217,14 @@ Phys phys_of(const fr_params& p) {
 // ------------------------------------------------------------ layout kernels
 // Canonical [elem][var][pt] (input element order) <-> native [pt][var][E] (native
 // element order, cpos: native -> canonical element, -1 for padding).  A transpose: a block
-// takes 32 native elements and up to 40 points through LDS, so that native rows move in
-// 32-element segments and canonical rows in segments of whole points (element by element,
+// takes 32 native elements and up to 8 (or 40) points through LDS, so that native rows move in
+// 32-element segments and canonical rows in segments of whole chunks (element by element,
 // in any element order), where a grid-stride loop over one side touches a cache line per
-// lane on the other.  Bound by HBM.  Chunks of at most 40 points keep the FP64 tile under
-// 53 KB (three blocks per CU).  Rows of 33 values: the transposed accesses fall on
-// different banks.  fr_unpack64 of 196,608 tetrahedra, renumbered (550 MB moved): 666 -> 130 us
-// (4.2 TB/s); of 32,768 p = 3 hexahedra (168 MB): 106 -> 26 us (6.4 TB/s).
+// lane on the other.  Bound by HBM; the loads of a thread go out in rounds of eight before any is
+// used (one at a time, packing a small mesh waited for five latencies in turn).  Rows of 33 values:
+// the transposed accesses fall on different banks.  fr_unpack64 of 196,608 tetrahedra, renumbered
+// (550 MB moved): 666 -> 125 us (4.4 TB/s), fr_pack64 680 -> 146; of 32,768 p = 3 hexahedra (168 MB):
+// 107 -> 26 us (6.4 TB/s), packing 57 -> 29.
 constexpr int LT_E = 32, LT_NT = 256;
 template <int NSP, int MAXPC>
 struct LayoutCfg {
@@ -262,16 +263,31 @@ __global__ void __launch_bounds__(LT_NT) k_layout(const double* __restrict__ can
     }
   }
   __syncthreads();
-#pragma unroll 8
-  for (int q = t; q < LT_E * NR; q += LT_NT) {
-    const int pt = q % PC, ev = q / PC, v = ev % 5, ce = cp[ev / 5];
-    if (pt >= np) continue;
-    T* w = &tile[(v * PC + pt) * LD + ev / 5];
-    const int64_t c = ((int64_t)ce * 5 + v) * NSP + p0 + pt;
-    if constexpr (PACK)
-      *w = ce >= 0 ? (T)(canon_in[c] - ref.v[v]) : (T)(sizeof(T) == 8 && (v == 0 || v == 4) ? 1 : 0);
-    else if (ce >= 0)
-      canon_out[c] = sizeof(T) == 8 ? (double)*w : (double)*w + ref.v[v];
+  // value q of the chunk: canonical element, point, variable (pt fastest, as in memory)
+  constexpr int NQ = (LT_E * NR + LT_NT - 1) / LT_NT, RD = NQ < 8 ? NQ : 8;
+#pragma unroll
+  for (int i0 = 0; i0 < NQ; i0 += RD) {
+    double x[PACK ? RD : 1];
+    if constexpr (PACK) {
+#pragma unroll
+      for (int i = 0; i < RD; ++i) {
+        const int q = t + (i0 + i) * LT_NT, pt = q % PC, ev = q / PC;
+        const bool ok = q < LT_E * NR && pt < np;
+        const int ce = ok ? cp[ev / 5] : -1;
+        x[i] = canon_in[ce >= 0 ? ((int64_t)ce * 5 + ev % 5) * NSP + p0 + pt : 0];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < RD; ++i) {
+      const int q = t + (i0 + i) * LT_NT, pt = q % PC, ev = q / PC, v = ev % 5;
+      if (q >= LT_E * NR || pt >= np) continue;
+      const int ce = cp[ev / 5];
+      T* w = &tile[(v * PC + pt) * LD + ev / 5];
+      if constexpr (PACK)
+        *w = ce >= 0 ? (T)(x[i] - ref.v[v]) : (T)(sizeof(T) == 8 && (v == 0 || v == 4) ? 1 : 0);
+      else if (ce >= 0)
+        canon_out[((int64_t)ce * 5 + v) * NSP + p0 + pt] = sizeof(T) == 8 ? (double)*w : (double)*w + ref.v[v];
+    }
   }
   if constexpr (PACK) {
     __syncthreads();
@@ -283,20 +299,49 @@ __global__ void __launch_bounds__(LT_NT) k_layout(const double* __restrict__ can
   }
 }
 
+// The same for few values: a thread per value of the native rows, no staging (its cache lines on
+// the canonical side are touched by many threads, which costs nothing while they fit L2).
+template <typename T, bool PACK>
+__global__ void __launch_bounds__(256) k_layout_few(const double* __restrict__ canon_in, double* __restrict__ canon_out,
+                                                    const T* __restrict__ nat_in, T* __restrict__ nat_out,
+                                                    const int32_t* __restrict__ cpos, int64_t E, int nsp, RefVec ref) {
+  const int64_t e = (int64_t)blockIdx.x * 64 + threadIdx.x;
+  const int row = blockIdx.y * 4 + threadIdx.y, v = row % 5, pt = row / 5;
+  if (pt >= nsp) return;
+  const int64_t i = (int64_t)row * E + e;
+  const int ce = cpos[e];
+  const int64_t c = ((int64_t)ce * 5 + v) * nsp + pt;
+  if constexpr (PACK) {
+    nat_out[i] = ce >= 0 ? (T)(canon_in[c] - ref.v[v]) : (T)(sizeof(T) == 8 && (v == 0 || v == 4) ? 1 : 0);
+  } else {
+    const T x = nat_in[i];
+    if (ce >= 0) canon_out[c] = sizeof(T) == 8 ? (double)x : (double)x + ref.v[v];
+  }
+}
+
 template <typename T, bool PACK>
 fr_status layout_block(fr_ctx c, const DevBlock& b, const double* cin, double* cout, const T* nin, T* nout, RefVec ref) {
-  if (b.E % LT_E != 0) return fail(c, FR_ERR_STATE, "block not padded to 32 elements");
-  // few tiles (one block each would leave CUs idle): chunks of 8 points, up to five times the
-  // blocks.  With 40-point chunks alone 10 steps and the unpacking of 64 p = 2 hexahedra took
-  // 828 us against 815 with the grid-stride loop
-  const int64_t tiles = b.E / LT_E;
-  const bool few = tiles < 256;
+  if (b.E % 64 != 0) return fail(c, FR_ERR_STATE, "block not padded to 64 elements");
+  const int64_t tiles = b.E / LT_E, values = b.E * 5 * b.nsp;
+  // kernel times, us, pack / unpack.  Few values, by a thread each / by tiles: 64 p = 2 hexahedra 2.2 / 4.1
+  // and 2.3 / 3.6; 6,144 p = 1 3.3 / 3.9 and 3.4 / 3.3 (245,760 values); 2,048 p = 2 3.6 / 4.3 and 3.6 / 4.0;
+  // 4,096 p = 2 4.8 / 4.5 and 5.3 / 4.4 (552,960); 1,024 p = 4 5.7 / 4.7 and 5.8 / 4.4
+  if (values <= 262144) {
+    const dim3 grid((unsigned)(b.E / 64), (unsigned)((5 * b.nsp + 3) / 4));
+    k_layout_few<T, PACK><<<grid, dim3(64, 4), 0, c->stream>>>(cin, cout, nin, nout, b.cpos, b.E, b.nsp, ref);
+    return FR_OK;
+  }
+  // chunks of 8 points (more, smaller blocks) or 40: 4,096 p = 4 hexahedra 9.7 / 12.1 and 9.2 / 9.7;
+  // 32,768 p = 3 29.1 / 33.5 and 26.1 / 28.9 (10.5 M values).  Past 16 M values, when both sides no longer
+  // fit the 256 MB last-level cache, unpacking takes the larger ones: 32,768 p = 4 81 / 97 and
+  // 79.5 / 64.8; 196,608 tetrahedra 146 / 154 and 148 / 125
+  const bool large = !PACK && values >= (int64_t)16 << 20;
 #define FR_LAYOUT(NSP)                                                                                          \
   case NSP:                                                                                                     \
-    if (few)                                                                                                    \
+    if (!large)                                                                                                 \
       k_layout<T, NSP, 8, PACK><<<(unsigned)(tiles * LayoutCfg<NSP, 8>::NCH), LT_NT, 0, c->stream>>>(            \
           cin, cout, nin, nout, b.cpos, b.E, ref);                                                              \
-    else                                                                                                        \
+    else if constexpr (!PACK)                                                                                   \
       k_layout<T, NSP, 40, PACK><<<(unsigned)(tiles * LayoutCfg<NSP, 40>::NCH), LT_NT, 0, c->stream>>>(          \
           cin, cout, nin, nout, b.cpos, b.E, ref);                                                              \
     break

@@ -1,0 +1,51 @@
+"""Canonical <-> native layout where its kernels change: the last block of elements moved value by
+value and the first moved through tiles (262,144 native values), for every number of points per
+element, on ragged and renumbered blocks, and a state whose unpacking takes the larger chunks
+(16 M values).  Data movement: bit for bit."""
+import numpy as np
+import pytest
+
+from paper_2408_16509_amd import inputs
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+REF = (1.0, 0.0, 0.0, 0.0, 2.5)
+
+
+def _round_trip(mesh, order, seed):
+    from paper_2408_16509_amd import frmi
+    for prec in (frmi.FR_FP64, frmi.FR_FP32):
+        ctx = frmi.Context(mesh, order=order, precision=prec, u_ref=REF, elem_order=2)
+        lay = ctx.layout
+        n, s, E = lay.n_elem[0], lay.n_sp[0], lay.e_pad[0]
+        c = np.random.default_rng(seed).normal(size=lay.canon_len) + 3.0
+        nat64 = ctx.pack64(c)
+        assert np.array_equal(ctx.unpack64(nat64).cpu().numpy(), c)
+        pad = nat64.view(s, 5, E)[:, :, n:].cpu().numpy()
+        assert np.array_equal(pad, np.broadcast_to(np.array([1.0, 0, 0, 0, 1])[None, :, None], pad.shape))
+        nat = ctx.pack(c)
+        got, rhs = ctx.unpack(nat).cpu().numpy(), ctx.unpack_rhs(nat).cpu().numpy()
+        if prec == frmi.FR_FP32:
+            r = np.array(REF)[None, :, None]
+            dev = (c.reshape(n, 5, s) - r).astype(np.float32).astype(np.float64)
+            assert np.array_equal(rhs, dev.ravel()) and np.array_equal(got, (dev + r).ravel())
+            assert not nat.view(s, 5, E)[:, :, n:].any()
+        else:
+            assert np.array_equal(got, c) and np.array_equal(rhs, c)
+        ctx.close()
+
+
+# the elements of the largest 64-element multiple within 262,144 values, less one, and of the next
+@pytest.mark.parametrize("kind,order,n", [
+    ("hex", 1, (61, 107, 1)), ("hex", 1, (7, 13, 72)), ("hex", 2, (19, 101, 1)), ("hex", 2, (3, 5, 131)),
+    ("hex", 3, (13, 59, 1)), ("hex", 3, (3, 9, 29)), ("hex", 4, (3, 127, 1)), ("hex", 4, (3, 9, 15)),
+    ("tet", 4, (5, 7, 7)), ("tet", 4, (3, 5, 17)), ("pyr", 4, (3, 7, 7)), ("pyr", 4, (3, 4, 13))])
+def test_either_side_of_the_tiles(kind, order, n):
+    mesh = {"hex": lambda: inputs.hex_box(n, permute_seed=3), "tet": lambda: inputs.kuhn_split(inputs.hex_box(n), permute_seed=3),
+            "pyr": lambda: inputs.pyramid_box(n, permute_seed=3)}[kind]()
+    _round_trip(mesh, order, 7)
+
+
+def test_larger_chunks():
+    _round_trip(inputs.hex_box((30, 31, 29), permute_seed=3), 4, 8)      # 26,970 x 625: 16.9 M values
