@@ -79,11 +79,13 @@ struct fr_ctx_s {
   int32_t* g_npos = nullptr;          // canonical -> native element index, all blocks [n_elem_total]
   std::vector<int32_t> h_cpos;        // native -> canonical element index, all blocks (host)
   int64_t canon_len = 0, native_len = 0;
-  // RK workspace: stage state and increment in the native dtype, FP64 accumulator
+  // RK workspace: stage state and the increment of one stage in the native dtype; FP64 form: the
+  // accumulator (the embedded pair's first increment) and that pair's second and third; FP32
+  // form: the increments of stages 1..3 block by block (see rk_inc, rk_accum)
   void* rk_stage = nullptr;
   double* rk_acc = nullptr;
   void* rk_k = nullptr;
-  void* rk_kk = nullptr;        // the increments of stages 1..3 (FP32 form; embedded pair)
+  void* rk_kk = nullptr;
   int* flag = nullptr;
   std::string err;
   // entropy filter / MLP workspace (canonical element order)
@@ -113,7 +115,7 @@ struct fr_ctx_s {
   void* tet_ogH = nullptr;    // BF16x3 split of the gradient operator: hi [TGR_M][TGR_K], then lo
   double* rk_x0 = nullptr;    // adaptive stepping in the FP32 form: u_n
   double* rk_part = nullptr;   // adaptive stepping: per-workgroup partial sums of the norm
-  double* rk_s64 = nullptr;   // FP64 stage state of the filtered FP32 form    // [TET_KP][TET_MP] transposed divergence operator
+  double* rk_s64 = nullptr;   // FP64 stage state of the filtered FP32 form
   int32_t* tet_src = nullptr;
   void* pyr_ops = nullptr;    // pyramids: It [55][85], Dt [3][55][55], Lt [85][55] in the context's type
   double* tet_ftab = nullptr; // entropy filter on tetrahedra: modal operators, weights, multiplicities
@@ -430,7 +432,8 @@ __global__ void k_to_dev(const double* __restrict__ u, float* __restrict__ w, in
 //   Y = x_i + dt a_{i+1,i} k_i  (the next stage state; in the native dtype, FP32 deviation in
 // the FP32 form).  x_i is summed again from the kept increments, in the registers' order, so
 // that a stage reads and writes neither a running state nor an error register, and the last
-// stage forms the new state, the saved u_n and the error norm in one pass.  Bound by its bytes,
+// stage forms the new state, the saved u_n and the error norm in one pass.  Padding lanes take no
+// increment (nothing writes theirs, and the buffers are shared with RK4's).  Bound by its bytes,
 // per FP64 value and attempt 152 instead of 208 (FP32 form 100 instead of
 // 180).  An attempt on 13,800 p = 3 Navier-Stokes hexahedra in FP64, right-hand sides included:
 // 864 -> 769 us.
@@ -442,14 +445,15 @@ struct LsK {
 
 template <typename KT, int I>
 __global__ void __launch_bounds__(256) k_lsrk_stage(const double* __restrict__ X, LsK<KT> A, KT* __restrict__ Y,
-                                                    int64_t E, int rows, RefVec ref) {
+                                                    int64_t E, int64_t n_real, int rows, RefVec ref) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= E) return;
+  const bool real = e < n_real;
   for (int row = blockIdx.y; row < rows; row += gridDim.y) {
     const int64_t i = (int64_t)row * E + e;
     double x = X[i], k[I + 1];
 #pragma unroll
-    for (int j = 0; j <= I; ++j) k[j] = (double)A.k[j][i];
+    for (int j = 0; j <= I; ++j) k[j] = real ? (double)A.k[j][i] : 0.0;
 #pragma unroll
     for (int j = 0; j < I; ++j) x = x + A.xb[j] * k[j];
     Y[i] = (KT)(x + A.ya * k[I] - (sizeof(KT) == 4 ? ref.v[row % 5] : 0.0));
@@ -471,7 +475,7 @@ __global__ void __launch_bounds__(256) k_lsrk_last(double* __restrict__ X, LsK<K
     const double x0 = X[i];
     double k[4], x = x0, err = 0.0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) k[j] = (double)A.k[j][i];
+    for (int j = 0; j < 4; ++j) k[j] = el < n_real ? (double)A.k[j][i] : 0.0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       x = x + A.xb[j] * k[j];
@@ -500,7 +504,8 @@ __global__ void __launch_bounds__(256) k_lsrk_last(double* __restrict__ X, LsK<K
 // The last stage adds them in FP64 in the accumulator's order, so the sums are the same bits.
 // HBM-bound: 84 bytes per value and step instead of 112.  Rows (blockIdx.y) of one variable,
 // so a value's reference entry costs no division by E; two values per thread (E is a
-// multiple of 64).  32,768 p = 3 hexahedra: 54.7 -> 39.8 us per stage on average.
+// multiple of 64).  Padding lanes take no increment (nothing writes theirs).  32,768 p = 3
+// hexahedra: 54.7 -> 39.8 us per stage on average.
 struct Rk32 {
   double* u;                                      // u_n, and the new state (last stage)
   const float *k1, *k2, *k3, *k;
@@ -509,19 +514,24 @@ struct Rk32 {
   double b1, b2, c;
 };
 template <bool LAST>
-__global__ void __launch_bounds__(256) k_rk32(Rk32 A, int64_t E, int rows, RefVec ref) {
+__global__ void __launch_bounds__(256) k_rk32(Rk32 A, int64_t E, int64_t n_real, int rows, RefVec ref) {
   const int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 2;
   if (e >= E) return;
+  const bool r0 = e < n_real, r1 = e + 1 < n_real;
+  auto inc = [&](const float* p, int64_t i) {
+    const float2 x = *reinterpret_cast<const float2*>(p + i);
+    return make_float2(r0 ? x.x : 0.0f, r1 ? x.y : 0.0f);
+  };
   for (int row = blockIdx.y; row < rows; row += gridDim.y) {
     const int64_t i = (int64_t)row * E + e;
     const double rv = ref.v[row % 5];
     const double u0 = A.u[i], u1 = A.u[i + 1];    // the caller's array: 8-byte alignment
-    const float2 k = *reinterpret_cast<const float2*>(A.k + i);
+    const float2 k = inc(A.k, i);
     double s0, s1;
     if constexpr (LAST) {
-      const float2 k1 = *reinterpret_cast<const float2*>(A.k1 + i);
-      const float2 k2 = *reinterpret_cast<const float2*>(A.k2 + i);
-      const float2 k3 = *reinterpret_cast<const float2*>(A.k3 + i);
+      const float2 k1 = inc(A.k1, i);
+      const float2 k2 = inc(A.k2, i);
+      const float2 k3 = inc(A.k3, i);
       s0 = rk4_sum(u0, k1.x, k2.x, k3.x, k.x, A.b1, A.b2);
       s1 = rk4_sum(u1, k1.y, k2.y, k3.y, k.y, A.b1, A.b2);
       A.u[i] = s0;
@@ -813,10 +823,11 @@ fr_status pyr_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
 }
 
 template <typename T, bool DEV>
-fr_status rhs_t(fr_ctx c, const T* u, T* r) {
-  for (auto& b : c->blocks) {
+fr_status rhs_t(fr_ctx c, const T* u, void* const* r) {
+  for (size_t bi = 0; bi < c->blocks.size(); ++bi) {
+    DevBlock& b = c->blocks[bi];
     const T* ub = u + b.native_off;
-    T* rb = r + b.native_off;
+    T* rb = (T*)r[bi];
     fr_status s = FR_OK;
     if (b.etype == FR_HEX) {
       switch (c->prm.order) {
@@ -836,10 +847,21 @@ fr_status rhs_t(fr_ctx c, const T* u, T* r) {
   return FR_OK;
 }
 
-// RHS of the context's precision on its native state.
+constexpr size_t kMaxBlocks = 2;
+
+// RHS of the context's precision on its native state, block i of it into r[i].
+fr_status rhs_blocks(fr_ctx c, const void* u, void* const* r) {
+  if (c->prm.precision != FR_FP64) return rhs_t<float, true>(c, (const float*)u, r);
+  return rhs_t<double, false>(c, (const double*)u, r);
+}
+
+size_t native_size(fr_ctx c) { return c->prm.precision != FR_FP64 ? sizeof(float) : sizeof(double); }
+
+// The same into one native array.
 fr_status rhs_native(fr_ctx c, const void* u, void* r) {
-  if (c->prm.precision != FR_FP64) return rhs_t<float, true>(c, (const float*)u, (float*)r);
-  return rhs_t<double, false>(c, (const double*)u, (double*)r);
+  void* rb[kMaxBlocks] = {};
+  for (size_t i = 0; i < c->blocks.size(); ++i) rb[i] = (char*)r + c->blocks[i].native_off * native_size(c);
+  return rhs_blocks(c, u, rb);
 }
 
 RefVec refvec(const fr_params& p) {
@@ -919,26 +941,37 @@ fr_status filter_alloc(fr_ctx c) {
 // An RK4 stage update fused into the filter's detection pass (see RkStageSrc): the
 // pass forms the stage state (or the new state) while checking it.
 struct StageFuse {
-  int mode = 0;                 // 0 first stage, 1 middle stages, 2 last (new state in place)
+  int stage = 0;                // 0..3; the last one updates u in place
   double b = 0, c = 0;          // accumulator and stage coefficients (times dt)
-  const void* k = nullptr;      // the stage's right-hand side, native dtype
-  bool k32 = false;             // k (and s32) FP32: the FP32 form
+  bool k32 = false;             // increments (and s32) FP32: the FP32 form
   double* u = nullptr;          // u_n, or the state updated in place (last stage)
-  double* acc = nullptr;        // FP64 accumulator
   double* s64 = nullptr;        // FP64 stage state written in full (FP64 form) or null
   float* s32 = nullptr;         // FP32 deviation of the stage state (FP32 form) or null
   double* cand64 = nullptr;     // FP64 stage state of the candidates only (FP32 form) or null
-  const float* kk = nullptr;    // FP32 form: the kept increments of stages 1..3, each kk_len long
-  int64_t kk_len = 0;
-  double b1 = 0, b2 = 0;        // their coefficients (times dt)
+  double b1 = 0, b2 = 0;        // FP32 form: the coefficients of the kept increments (times dt)
 };
 
+// Increment of RK stage s (0..3) of a block.  FP64: 0 shares RK4's accumulator, which RK4 writes
+// before it reads it (the embedded pair keeps all of them, RK4 uses 3 alone).
+char* rk_inc(fr_ctx c, const DevBlock& b, int s) {
+  const int64_t o = b.native_off, len = (int64_t)b.nsp * 5 * b.E;
+  if (s == 3) return (char*)c->rk_k + o * native_size(c);
+  if (c->prm.precision != FR_FP64) return (char*)((float*)c->rk_kk + 3 * o + s * len);
+  return (char*)(s == 0 ? c->rk_acc + o : (double*)c->rk_kk + (s - 1) * c->native_len + o);
+}
+
+// FP64 accumulator of a block.  In the FP32 form only filtered hexahedra keep one, over the
+// increments that they do not keep (two FP32 arrays).
+double* rk_accum(fr_ctx c, const DevBlock& b) {
+  return c->prm.precision != FR_FP64 ? (double*)((float*)c->rk_kk + 3 * b.native_off) : c->rk_acc + b.native_off;
+}
+
 template <typename KT>
-RkStageSrc<KT> stage_src(const StageFuse& z, const DevBlock& b, const fr_params& prm) {
+RkStageSrc<KT> stage_src(fr_ctx c, const StageFuse& z, const DevBlock& b) {
   const int64_t o = b.native_off;
-  RkStageSrc<KT> s{z.u + o, (const KT*)z.k + o, z.acc + o, z.s64 ? z.s64 + o : nullptr,
-                   z.s32 ? z.s32 + o : nullptr, z.b, z.c, z.mode, {0, 0, 0, 0, 0}};
-  for (int v = 0; v < 5; ++v) s.ref[v] = prm.u_ref[v];
+  RkStageSrc<KT> s{z.u + o, (const KT*)rk_inc(c, b, 3), rk_accum(c, b), z.s64 ? z.s64 + o : nullptr,
+                   z.s32 ? z.s32 + o : nullptr, z.b, z.c, z.stage == 0 ? 0 : (z.stage < 3 ? 1 : 2), {0, 0, 0, 0, 0}};
+  for (int v = 0; v < 5; ++v) s.ref[v] = c->prm.u_ref[v];
   return s;
 }
 
@@ -979,10 +1012,10 @@ void hex_candidates_p(fr_ctx c, DevBlock& b, const double* u, const StageFuse* f
       hex_filter_detect_lines<P, PlainSrc><<<g, 256, 0, c->stream>>>(PlainSrc{u + b.native_off}, b.smin, b.E,
                                                                      b.n, K, F, L);
     else if (fz->k32)
-      hex_filter_detect_lines<P, RkStageSrc<float>><<<g, 256, 0, c->stream>>>(stage_src<float>(*fz, b, c->prm),
+      hex_filter_detect_lines<P, RkStageSrc<float>><<<g, 256, 0, c->stream>>>(stage_src<float>(c, *fz, b),
                                                                               b.smin, b.E, b.n, K, F, L);
     else
-      hex_filter_detect_lines<P, RkStageSrc<double>><<<g, 256, 0, c->stream>>>(stage_src<double>(*fz, b, c->prm),
+      hex_filter_detect_lines<P, RkStageSrc<double>><<<g, 256, 0, c->stream>>>(stage_src<double>(c, *fz, b),
                                                                                b.smin, b.E, b.n, K, F, L);
   } else {
     const unsigned g = (unsigned)(b.E / HexTileCfg<P>::NE);
@@ -991,16 +1024,16 @@ void hex_candidates_p(fr_ctx c, DevBlock& b, const double* u, const StageFuse* f
                                                                              b.E, b.n, K, F, L, nullptr);
     else if (fz->k32)
       hex_filter_detect<P, RkStageSrc<float>><<<g, HexTileCfg<P>::NT, 0, c->stream>>>(
-          stage_src<float>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, L,
+          stage_src<float>(c, *fz, b), b.smin, b.E, b.n, K, F, L,
           fz->cand64 ? fz->cand64 + b.native_off : nullptr);
     else
       hex_filter_detect<P, RkStageSrc<double>><<<g, HexTileCfg<P>::NT, 0, c->stream>>>(
-          stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, K, F, L,
+          stage_src<double>(c, *fz, b), b.smin, b.E, b.n, K, F, L,
           fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   }
   if (P == 4 && fz && fz->cand64 && fz->k32)
     k_cand_stage<float><<<(unsigned)std::max<int64_t>(1, std::min<int64_t>(b.n, 4096)), 256, 0, c->stream>>>(
-        stage_src<float>(*fz, b, c->prm), b.f_list, b.f_cnt + c->f_slot, b.nsp * 5, b.E, fz->cand64 + b.native_off);
+        stage_src<float>(c, *fz, b), b.f_list, b.f_cnt + c->f_slot, b.nsp * 5, b.E, fz->cand64 + b.native_off);
   c->prof_end(pk);
 }
 
@@ -1064,15 +1097,16 @@ void tet_candidates(fr_ctx c, DevBlock& b, const double* u, const StageFuse* fz 
                                                            nullptr);
   else if (fz->k32) {
     const int64_t o = b.native_off;
-    RkKeepSrc src{fz->u + o, (const float*)fz->k + o, fz->kk + o, fz->kk + fz->kk_len + o, fz->kk + 2 * fz->kk_len + o,
-                  fz->s32 + o, fz->b1, fz->b2, fz->c, fz->mode == 2, {0, 0, 0, 0, 0}};
+    auto inc = [&](int s) { return (const float*)rk_inc(c, b, s); };
+    RkKeepSrc src{fz->u + o, inc(fz->stage), inc(0), inc(1), inc(2),
+                  fz->s32 + o, fz->b1, fz->b2, fz->c, fz->stage == 3, {0, 0, 0, 0, 0}};
     for (int v = 0; v < 5; ++v) src.ref[v] = c->prm.u_ref[v];
     tet_filter_detect<RkKeepSrc><<<gE, TF_NT, 0, c->stream>>>(src, b.smin, b.E, b.n, F, L,
                                                               fz->cand64 ? fz->cand64 + o : nullptr);
   }
   else
     tet_filter_detect<RkStageSrc<double>><<<gE, TF_NT, 0, c->stream>>>(
-        stage_src<double>(*fz, b, c->prm), b.smin, b.E, b.n, F, L,
+        stage_src<double>(c, *fz, b), b.smin, b.E, b.n, F, L,
         fz->cand64 ? fz->cand64 + b.native_off : nullptr);
   c->prof_end(pk);
 }
@@ -1764,26 +1798,23 @@ fr_status fr_rhs(fr_ctx c, const void* u, void* r) {
 }  // extern "C"
 
 namespace {
-// RK workspace: stage state and increment in the native dtype, and as asked the FP64
-// accumulator and the kept increments of the FP32 form.  Padding lanes are never written
-// by the RHS: all start at zero.
-fr_status rk_alloc(fr_ctx c, bool acc, bool kept) {
+// RK workspace.  Padding lanes of the increments are never written by the RHS and start at zero.
+// What either integrator needs of the first call on is allocated by it whatever the filter
+// (a later call with another one then allocates nothing of it), the embedded pair's own apart.
+fr_status rk_alloc(fr_ctx c, bool pair) {
   const int64_t n = c->native_len;
-  const size_t tsz = c->prm.precision != FR_FP64 ? sizeof(float) : sizeof(double);
-  if (!c->rk_stage) {
-    if (dalloc(c, (char**)&c->rk_stage, n * tsz) || dalloc(c, (char**)&c->rk_k, n * tsz)) return FR_ERR_ALLOC;
-    HIP_TRY(c, hipMemsetAsync(c->rk_k, 0, n * tsz, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->rk_stage, 0, n * tsz, c->stream));
-  }
-  if (acc && !c->rk_acc) {
-    if (dalloc(c, &c->rk_acc, n)) return FR_ERR_ALLOC;
-    HIP_TRY(c, hipMemsetAsync(c->rk_acc, 0, n * sizeof(double), c->stream));
-  }
-  if (kept && !c->rk_kk) {
-    if (dalloc(c, (char**)&c->rk_kk, 3 * n * tsz)) return FR_ERR_ALLOC;
-    HIP_TRY(c, hipMemsetAsync(c->rk_kk, 0, 3 * n * tsz, c->stream));
-  }
-  return FR_OK;
+  const bool f32 = c->prm.precision != FR_FP64;
+  auto get = [&](void** p, size_t bytes) -> fr_status {
+    if (*p) return FR_OK;
+    if (dalloc(c, (char**)p, bytes)) return FR_ERR_ALLOC;
+    HIP_TRY(c, hipMemsetAsync(*p, 0, bytes, c->stream));
+    return FR_OK;
+  };
+  fr_status st;
+  if ((st = get(&c->rk_stage, n * native_size(c))) || (st = get(&c->rk_k, n * native_size(c)))) return st;
+  if (f32) return get(&c->rk_kk, 3 * n * sizeof(float));
+  if ((st = get((void**)&c->rk_acc, n * sizeof(double)))) return st;
+  return pair ? get(&c->rk_kk, 2 * n * sizeof(double)) : FR_OK;
 }
 
 // RK3(2)4[2R+]C (Kennedy, Carpenter & Lewis 2000): subdiagonal, weights, embedded weights.
@@ -1818,7 +1849,7 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
       !(ap->fac_min <= 1) || !(ap->fac_max >= 1) || !std::isfinite(ap->fac_max) || ap->max_attempts < 1)
     return fail(c, FR_ERR_ARG, "adaptive parameters out of range");
   fr_status st;
-  if ((st = rk_alloc(c, false, true))) return st;
+  if ((st = rk_alloc(c, true))) return st;
   const int64_t n = c->native_len;
   if (!c->rk_part && dalloc(c, &c->rk_part, (int64_t)kNormGrid * (int64_t)c->blocks.size())) return FR_ERR_ALLOC;
   if (c->prm.precision != FR_FP64 && !c->rk_x0 && dalloc(c, &c->rk_x0, n)) return FR_ERR_ALLOC;
@@ -1830,9 +1861,6 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
   std::vector<double> part(c->blocks.size() * kNormGrid);
   // u_n for a rejected step: in FP64 the stage state's buffer, which the last stage has read
   double* X0 = f32 ? c->rk_x0 : (double*)c->rk_stage;
-  auto k_of = [&](int i) -> void* {
-    return i == 3 ? c->rk_k : (void*)((char*)c->rk_kk + (size_t)i * n * (f32 ? sizeof(float) : sizeof(double)));
-  };
   // one stage update on every block
   auto stage_t = [&](int i, double h, auto kt) {
     using KT = decltype(kt);
@@ -1841,7 +1869,7 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
       const int64_t o = b.native_off;
       LsK<KT> A;
       for (int j = 0; j < 4; ++j) {
-        A.k[j] = (const KT*)k_of(j) + o;
+        A.k[j] = (const KT*)rk_inc(c, b, j);
         A.xb[j] = h * (kLsB[j][0] / kLsB[j][1]);
         A.ed[j] = h * (kLsB[j][0] / kLsB[j][1] - kLsBh[j][0] / kLsBh[j][1]);
       }
@@ -1849,9 +1877,9 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
       const int rows = b.nsp * 5, nt = b.E >= 512 ? 256 : 64;
       const dim3 grid((unsigned)((b.E + nt - 1) / nt), (unsigned)rows);
       KT* Y = (KT*)c->rk_stage + o;
-      if (i == 0) k_lsrk_stage<KT, 0><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, rows, ref);
-      else if (i == 1) k_lsrk_stage<KT, 1><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, rows, ref);
-      else if (i == 2) k_lsrk_stage<KT, 2><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, rows, ref);
+      if (i == 0) k_lsrk_stage<KT, 0><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, b.n, rows, ref);
+      else if (i == 1) k_lsrk_stage<KT, 1><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, b.n, rows, ref);
+      else if (i == 2) k_lsrk_stage<KT, 2><<<grid, nt, 0, c->stream>>>(X + o, A, Y, b.E, b.n, rows, ref);
       else
         k_lsrk_last<KT><<<kNormGrid, 256, 0, c->stream>>>(X + o, A, X0 + o, rows * b.E, b.E, b.n, ap->atol, ap->rtol,
                                                           c->rk_part + bi * kNormGrid);
@@ -1878,7 +1906,9 @@ fr_status fr_rk_adaptive(fr_ctx c, void* u_, double t_end, double dt0, const fr_
           in = X;
         }
       }
-      if ((st = rhs_native(c, in, k_of(i)))) return st;
+      void* ks[kMaxBlocks] = {};
+      for (size_t bi = 0; bi < c->blocks.size(); ++bi) ks[bi] = rk_inc(c, c->blocks[bi], i);
+      if ((st = rhs_blocks(c, in, ks))) return st;
       stage(i, h);
     }
     HIP_TRY(c, hipGetLastError());
@@ -1923,10 +1953,7 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
   const int64_t n = c->native_len;
   const bool f32 = c->prm.precision != FR_FP64;
   fr_status st;
-  // the FP32 form keeps its increments; its filtered hexahedra use the accumulator
-  bool acc = !f32;
-  for (auto& b : c->blocks) acc = acc || (filter_mode >= 0 && b.etype == FR_HEX);
-  if ((st = rk_alloc(c, acc, f32))) return st;
+  if ((st = rk_alloc(c, false))) return st;
   const int g = grid_for(n, 256);
   const double b1 = dt / 6.0, b2 = dt / 3.0, c2 = dt / 2.0;
   int pk;
@@ -1941,12 +1968,10 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
         for (int stage = 0; stage < 4; ++stage) {
           if ((st = rhs_native(c, stage == 0 ? u : S, K))) return st;
           StageFuse fz;
-          fz.mode = stage == 0 ? 0 : (stage < 3 ? 1 : 2);
+          fz.stage = stage;
           fz.b = stage == 0 || stage == 3 ? b1 : b2;
           fz.c = stage == 2 ? dt : c2;
-          fz.k = K;
           fz.u = u;
-          fz.acc = c->rk_acc;
           fz.s64 = stage < 3 ? S : nullptr;
           if ((st = apply_filter(c, stage < 3 ? S : u, filter_mode, nullptr, &fz))) return st;
         }
@@ -1979,8 +2004,16 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
       if (filt && (st = apply_filter(c, u, filter_mode))) return st;
     }
   } else {
-    float *K = (float*)c->rk_k, *S = (float*)c->rk_stage, *KK = (float*)c->rk_kk;
+    float* S = (float*)c->rk_stage;
     const RefVec ref = refvec(c->prm);
+    // the right-hand side of a stage into its kept increment; the fused hexahedral filter, which
+    // keeps an accumulator instead, reads the stage's own alone
+    auto stage_rhs = [&](int stage, bool fused) {
+      void* ks[kMaxBlocks] = {};
+      for (size_t bi = 0; bi < c->blocks.size(); ++bi)
+        ks[bi] = rk_inc(c, c->blocks[bi], fused && c->blocks[bi].etype == FR_HEX ? 3 : stage);
+      return rhs_blocks(c, S, ks);
+    };
     // the FP32 deviation of u_n; later steps get it from the previous step's last update
     for (auto& b : c->blocks) {
       const int64_t nb = (int64_t)b.nsp * 5 * b.E;
@@ -1998,20 +2031,15 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
         for (int s = 0; s < n_steps; ++s) {
           if ((st = compute_smin(c, u))) return st;
           for (int stage = 0; stage < 4; ++stage) {
-            float* ks = stage < 3 ? KK + (int64_t)stage * n : K;
-            if ((st = rhs_native(c, S, ks))) return st;
+            if ((st = stage_rhs(stage, true))) return st;
             StageFuse fz;
-            fz.mode = stage == 0 ? 0 : (stage < 3 ? 1 : 2);
+            fz.stage = stage;
             fz.b = stage == 0 || stage == 3 ? b1 : b2;
             fz.c = stage == 2 ? dt : c2;
-            fz.k = ks;
             fz.k32 = true;
-            fz.kk = KK;
-            fz.kk_len = n;
             fz.b1 = b1;
             fz.b2 = b2;
             fz.u = u;
-            fz.acc = c->rk_acc;
             fz.s32 = S;
             fz.cand64 = stage < 3 ? S64 : nullptr;
             if ((st = apply_filter(c, stage < 3 ? S64 : u, filter_mode, S, &fz))) return st;
@@ -2026,17 +2054,17 @@ fr_status fr_rk_step(fr_ctx c, void* u_, double dt, int32_t n_steps, int32_t fil
     for (int s = 0; s < n_steps; ++s) {
       if (filter_mode >= 0 && (st = compute_smin(c, u))) return st;
       for (int stage = 0; stage < 4; ++stage) {
-        float* ks = stage < 3 ? KK + (int64_t)stage * n : K;
-        if ((st = rhs_native(c, S, ks))) return st;
+        if ((st = stage_rhs(stage, false))) return st;
         pk = c->prof_begin("rk4_update_f32");
         for (auto& b : c->blocks) {
           const int64_t o = b.native_off;
           const int rows = b.nsp * 5, nt = b.E >= 512 ? 256 : 32;
           const dim3 grid((unsigned)((b.E / 2 + nt - 1) / nt), (unsigned)rows);
-          const Rk32 A{u + o, KK + o, KK + n + o, KK + 2 * n + o, ks + o, S + o, filter_mode >= 0 ? c->rk_s64 + o : nullptr,
+          auto inc = [&](int s) { return (const float*)rk_inc(c, b, s); };
+          const Rk32 A{u + o, inc(0), inc(1), inc(2), inc(stage), S + o, filter_mode >= 0 ? c->rk_s64 + o : nullptr,
                        b1, b2, stage == 2 ? dt : c2};
-          if (stage < 3) k_rk32<false><<<grid, nt, 0, c->stream>>>(A, b.E, rows, ref);
-          else k_rk32<true><<<grid, nt, 0, c->stream>>>(A, b.E, rows, ref);
+          if (stage < 3) k_rk32<false><<<grid, nt, 0, c->stream>>>(A, b.E, b.n, rows, ref);
+          else k_rk32<true><<<grid, nt, 0, c->stream>>>(A, b.E, b.n, rows, ref);
         }
         c->prof_end(pk);
         if (filter_mode >= 0 && (st = apply_filter(c, stage < 3 ? c->rk_s64 : u, filter_mode, S))) return st;
