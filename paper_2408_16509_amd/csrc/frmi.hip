@@ -50,10 +50,11 @@ struct DevBlock {
   void* geo_t = nullptr;    // geometry in the kernels' arithmetic type (== geo for FP64)
   int32_t* nbr_elem = nullptr;
   int32_t* nbr_info = nullptr;
-  void* uf = nullptr;       // [nfp][5][E]
-  void* grad = nullptr;     // [nsp][15][E]; hexahedra: the points' viscous flux, [nsp][9][E]
-  void* gradf = nullptr;    // [nfp][15][E]; hexahedra: f_v.n, [nfp][4][E]
-  void* fc = nullptr;       // [nfp][5][E] common fluxes (Navier--Stokes)
+  void* uf = nullptr;       // [nfp][5][E] traces of u (not tetrahedra)
+  void* grad = nullptr;     // gradient [nsp][15][E]; hexahedra, and where common fluxes are formed once per
+                            // pair: the points' viscous flux, [nsp][9][E], 12 values by tile
+  void* gradf = nullptr;    // hexahedra: f_v.n, [nfp][4][E]; two-sided pyramids: gradient traces [nfp][15][E]
+  void* fc = nullptr;       // [nfp][5][E] common fluxes, where they are stored
   void* cmet = nullptr;     // curved hexahedra: stored metric terms in the kernels' type (else NULL)
   int64_t elem_off = 0;     // offset of the block in the element numbering (both orders)
   int32_t* cpos = nullptr;  // native index -> canonical index within the block [E] (-1: padding)
@@ -614,6 +615,10 @@ RefState<T> ref_of(const fr_params& p) {
 
 int side_mode_of(double beta) { return beta == 0.5 ? 1 : (beta == -0.5 ? -1 : 0); }
 
+// Tetrahedra whose gradient kernel forms the common fluxes, once per pair: a one-sided switch
+// (side_mode != 0), FP32 or straight elements (see tet_rhs).
+constexpr bool tet_can_pair(bool f32, bool curved) { return f32 || !curved; }
+
 template <typename T, bool DEV, int P, bool CUR>
 fr_status hex_rhs_p(fr_ctx c, DevBlock& b, const T* u, T* r) {
   constexpr int N1 = P + 1, NE = HexCfg<P>::NE, NT = NE * N1 * N1;
@@ -720,7 +725,7 @@ fr_status tet_rhs(fr_ctx c, DevBlock& b, const T* u, T* r) {
     // divergence 137 -> 76).  Not for FP64 curved elements, whose two sides' stored normals
     // agree to rounding only: one side's unit normal on both moved the low-Mach residual
     // by 1e-9, beyond its rounding floor
-    constexpr bool can_fc = sizeof(T) == 4 || !CUR;
+    constexpr bool can_fc = tet_can_pair(sizeof(T) == 4, CUR);
     const bool fc = sm != 0 && can_fc;
     T* fcb = (T*)b.fc;
     const T gam = (T)p.gamma, mu = (T)p.mu, pr = (T)p.prandtl, beta = (T)p.ldg_beta, tau = (T)p.ldg_tau;
@@ -1402,15 +1407,21 @@ fr_status setup_impl(const fr_params* p, int64_t n_vert, const double* xyz, cons
       }
     }
     if (dalloc(c, &d.geo, hb.geo.size()) || dalloc(c, &d.nbr_elem, hb.nbr_elem.size()) ||
-        dalloc(c, &d.nbr_info, hb.nbr_info.size()) || dalloc(c, (char**)&d.uf, (size_t)d.nfp * 5 * d.E * tsz))
+        dalloc(c, &d.nbr_info, hb.nbr_info.size()))
       return bail(FR_ERR_ALLOC);
-    const bool is_tet = d.etype == FR_TET, is_hex = d.etype == FR_HEX;
-    if (p->system == FR_NAVIER_STOKES &&
-        (dalloc(c, (char**)&d.grad, (size_t)d.nsp * (is_hex ? 9 : 15) * d.E * tsz) ||
-         (!is_tet && dalloc(c, (char**)&d.gradf, (size_t)d.nfp * (is_hex ? 4 : 15) * d.E * tsz))))
-      return bail(FR_ERR_ALLOC);
-    if (p->system == FR_NAVIER_STOKES && dalloc(c, (char**)&d.fc, (size_t)d.nfp * 5 * d.E * tsz))
-      return bail(FR_ERR_ALLOC);
+    // what the kernels of this context's form read: traces of u except on tetrahedra (their flux
+    // points are solution points); Navier--Stokes: the points' viscous flux (hexahedra 9 values, with
+    // once-per-pair common fluxes 12) or gradient (15), the gradient's traces (hexahedra f_v.n, pyramids
+    // with a two-sided switch), the common fluxes where they are stored
+    const bool is_tet = d.etype == FR_TET, is_hex = d.etype == FR_HEX, ns = p->system == FR_NAVIER_STOKES;
+    const bool pair = side_mode_of(p->ldg_beta) != 0 &&
+                      (!is_tet || tet_can_pair(tsz == sizeof(float), !hb.cmet.empty()));
+    const int rows_fp[3] = {is_tet ? 0 : 5, !ns || is_tet ? 0 : (is_hex ? 4 : (pair ? 0 : 15)), ns && (is_hex || pair) ? 5 : 0};
+    const int rows_sp = !ns ? 0 : (is_hex ? 9 : (pair ? 12 : 15));
+    void** const at_fp[3] = {&d.uf, &d.gradf, &d.fc};
+    for (int k = 0; k < 3; ++k)
+      if (rows_fp[k] && dalloc(c, (char**)at_fp[k], (size_t)d.nfp * rows_fp[k] * d.E * tsz)) return bail(FR_ERR_ALLOC);
+    if (rows_sp && dalloc(c, (char**)&d.grad, (size_t)d.nsp * rows_sp * d.E * tsz)) return bail(FR_ERR_ALLOC);
     d.geo_t = d.geo;
     if (tsz == sizeof(float)) {
       std::vector<float> g32(hb.geo.begin(), hb.geo.end());
