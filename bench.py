@@ -157,13 +157,18 @@ def kernel_bytes_per_elem(name, nsp, nfp):
         "hex_grad_vf": d * (5 * nsp + 5 * nfp // 2 + 9 * nsp + 4 * nfp // 2) + hex_geo + hex_conn,
         "hex_face_vf": d * (5 * nfp + 4 * nfp // 2 + 5 * nfp) + hex_geo + hex_conn,
         "hex_div_vf": d * (5 * nsp + 9 * nsp + 5 * nfp + 5 * nsp) + hex_geo,
-        # the same steps with the gradient and its traces stored (15 words each)
+        # the same steps with the gradient and its traces stored (15 words each): the kernels of the
+        # recorded profiles that carry these names; none of them runs now
         "hex_grad": d * (5 * nsp + 5 * nfp // 2 + 15 * nsp + 15 * nfp // 2) + hex_geo + hex_conn,
         "hex_face_ns": d * (5 * nfp + 15 * nfp // 2 + 5 * nfp) + hex_geo + hex_conn,
         "hex_div_ns": d * (5 * nsp + 15 * nsp + 5 * nfp + 5 * nsp) + hex_geo,
         "tet_div_euler": d * (5 * nsp + 5 * nsp) + tet_gc,
-        "tet_grad": d * (5 * nsp + 15 * nsp) + tet_gc,
-        "tet_div_ns": d * (5 * nsp + 15 * nsp + 5 * nsp) + tet_gc,
+        # straight tetrahedra, one-sided LDG, both precisions: the gradient kernel stores the
+        # transformed viscous flux S_i . f_v (12 words per point) and the common flux of each
+        # flux-point pair once (half of the flux points); the divergence kernel reads both, the
+        # common flux for all of its flux points
+        "tet_grad": d * (5 * nsp + 12 * nsp + 5 * nfp // 2) + tet_gc,
+        "tet_div_ns": d * (5 * nsp + 12 * nsp + 5 * nsp + 5 * nfp) + tet_gc,
         # pyramids: traces of u stored for every flux point (read by both sides); with the
         # one-sided switch the gradient kernel reads both traces where it forms the pair's
         # common flux (half of the flux points) and stores that flux and S_i . f_v at the
@@ -173,13 +178,6 @@ def kernel_bytes_per_elem(name, nsp, nfp):
         "pyr_grad": d * (5 * nsp + 5 * nfp + 12 * nsp + 5 * nfp // 2) + pyr_gc,
         "pyr_div_ns": d * (5 * nsp + 12 * nsp + 5 * nfp + 5 * nsp) + pyr_gc,
     }
-    if d == 4:
-        # FP32 form, one-sided LDG: the gradient kernel stores the transformed viscous flux
-        # S_i . f_v (12 values per point) instead of the gradient (15) and the common flux
-        # of each flux-point pair once (half of the flux points); the divergence kernel
-        # reads both, the common flux for all of its flux points
-        table["tet_grad"] = d * (5 * nsp + 12 * nsp + 5 * nfp // 2) + tet_gc
-        table["tet_div_ns"] = d * (5 * nsp + 12 * nsp + 5 * nsp + 5 * nfp) + tet_gc
     return table.get(fam)
 
 
