@@ -355,7 +355,7 @@ def run_adaptive_workload(cfg, args, torch, np, frmi, inputs):
         ev1.record(stream)
         torch.cuda.synchronize()
         ms_f = ev0.elapsed_time(ev1)
-        diff = float(torch.linalg.norm(uf - u) / torch.linalg.norm(u - u0))
+        diff = _rel_l2(uf - u, u - u0, torch)
         out_forms[form] = {
             "gdof_s": round(dof * st.n_rhs / (ms_a * 1e-3) / 1e9, 4), "time_to_t_end_ms": round(ms_a, 3),
             "accepted": int(st.accepted), "rejected": int(st.rejected), "n_rhs": int(st.n_rhs),
@@ -460,7 +460,7 @@ def run_filter_workload(cfg, args, torch, np, frmi, inputs):
             runs[f"{form}_{name}"] = {"ms": ms, "u": u, "times": times, "finite": cx.check(u)}
     ref_u = runs["fp64_plain"]["u"]
     for k_, r_ in runs.items():
-        r_["sol_rel_l2_vs_fp64_plain"] = float(torch.linalg.norm(r_["u"] - ref_u) / torch.linalg.norm(ref_u))
+        r_["sol_rel_l2_vs_fp64_plain"] = _rel_l2(r_["u"] - ref_u, ref_u, torch)
     # filter statistics on stage-like states: one unfiltered step from points of the trajectory
     probe = {"plain": [0, 0, 0, 0], "mlp": [0, 0, 0, 0]}
     k_equal, k_total, filt_ms = 0, 0, {"plain": [], "mlp": []}
@@ -533,10 +533,17 @@ def run_filter_workload(cfg, args, torch, np, frmi, inputs):
     return out
 
 
+def _rel_l2(diff, ref, torch):
+    """|diff| / |ref| of device tensors, on the host (see _per_var_err)."""
+    return float(torch.linalg.norm(diff.cpu()) / torch.linalg.norm(ref.cpu()))
+
+
 def _per_var_err(a, b, blocks, torch):
     """Relative L2 error per conservative variable of canonical arrays (blocks of
-    [n][5][nsp], in block order).  Summed on the host: the device's strided sum over
-    (0, 2) returned a wrong momentum in 60 of 200 repeats on the same 82,944 x 5 x 55 arrays."""
+    [n][5][nsp], in block order).  Summed on the host: torch's sum over (0, 2) on the device
+    joins its blocks' partial sums wrongly when two different sums alternate (a program of torch
+    alone, without this library, on 82,944 x 5 x 55 arrays: 26 wrong of 200 pairs; the same sum
+    again and again 0 of 200, its stale partials being the right ones)."""
     num = torch.zeros(5, dtype=torch.float64)
     den = torch.zeros(5, dtype=torch.float64)
     o = 0
@@ -716,7 +723,7 @@ def run_tgv_workload(name, cfg, forms, args, torch, np, frmi, inputs, with_cpu=T
             rr, uu = runs[f]["rhs0"], runs[f]["u_final"]
             pv = _per_var_err(rr, r64, runs[f]["blocks"], torch)
             o = out["forms"][f]
-            o["rhs_rel_l2_vs_fp64_form"] = float(torch.linalg.norm(rr - r64) / torch.linalg.norm(r64))
+            o["rhs_rel_l2_vs_fp64_form"] = _rel_l2(rr - r64, r64, torch)
             o["rhs_rel_l2_vs_fp64_form_per_var"] = pv
             o["rhs_meets_1e-5_per_var"] = [v <= ERR_TARGET_PER_RHS for v in pv]
             bound = STATED_RHS_BOUND.get((name, f.split(":")[0]))
@@ -725,7 +732,7 @@ def run_tgv_workload(name, cfg, forms, args, torch, np, frmi, inputs, with_cpu=T
                 o["rhs_within_stated_bound"] = bool(all(v <= b for v, b in zip(pv, bound)))
             o["solution_rel_l2_vs_fp64_form"] = {
                 "against": ref, "steps": runs[f]["steps_total"],
-                "value": float(torch.linalg.norm(uu - u64) / torch.linalg.norm(u64))}
+                "value": _rel_l2(uu - u64, u64, torch)}
     if not args.no_kernel_timing:
         out["roofline"] = roofline_for(head["times"], blocks, forms[0])
         out["roofline"]["traffic"] = load_traffic(out["roofline"]["kernel"], name)
