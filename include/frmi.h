@@ -134,8 +134,8 @@ typedef struct {
 /* Adaptive time stepping (Sec. "Adaptive time stepping": low-storage Runge--Kutta with
  * an embedded pair; the error estimate of each step, normalised, decides acceptance and
  * the next step size).  Scheme: the third-order, four-stage pair with a second-order
- * embedded solution RK3(2)4[2R+]C of Kennedy, Carpenter & Lewis (2000), carried in the
- * two-register "2R+" form plus an error register.  Norm: RMS over all values of
+ * embedded solution RK3(2)4[2R+]C of Kennedy, Carpenter & Lewis (2000), its stage increments
+ * kept and the new state and the error formed from them.  Norm: RMS over all values of
  * e / (atol + rtol max(|u_n|, |u_{n+1}|)), e = u_{n+1} - u^_{n+1}; accepted if <= 1;
  * next step dt min(fac_max, max(fac_min, safety norm^(-1/3))) (fac_min if the norm is
  * not finite); the last step is shortened to land on t_end. */
@@ -278,11 +278,11 @@ void fr_default_adaptive_params(fr_adaptive_params* p);
 /* Advance the FP64 native state u (in place) from t = 0 to t_end with adaptive steps
  * of the embedded pair above, starting from the step size dt0; rejected steps restore
  * u_n.  In the FP32 form the right-hand sides run on FP32 deviations while the state,
- * the stage registers' FP64 parts, the error register and the norm are FP64.  No
- * entropy filter.  stats (host) receives the counts; the call synchronises once per
- * attempted step (the norm decides on the host).  Errors: FR_ERR_ARG (NULL, t_end or
- * dt0 not positive and finite, parameters out of range), FR_ERR_ALLOC, FR_ERR_DEVICE;
- * a non-finite norm counts as a rejected step (the controller shrinks dt). */
+ * the stage sums, the error and the norm are FP64.  No entropy filter.  stats (host)
+ * receives the counts; the call synchronises once per attempted step (the norm decides
+ * on the host).  Errors: FR_ERR_ARG (NULL, t_end or dt0 not positive and finite,
+ * parameters out of range), FR_ERR_ALLOC, FR_ERR_DEVICE; a non-finite norm counts as a
+ * rejected step (the controller shrinks dt). */
 fr_status fr_rk_adaptive(fr_ctx ctx, void* u_dev, double t_end, double dt0, const fr_adaptive_params* prm,
                          fr_adaptive_stats* stats);
 
@@ -361,7 +361,7 @@ fr_status fr_check(fr_ctx ctx, const void* u_dev);
  * fr_profile(ctx, 1) clears and enables, fr_profile(ctx, 0) disables.
  * fr_profile_read synchronises and fills up to cap records (host). */
 typedef struct {
-  char name[48];           /* kernel family, e.g. "hex_div_ns_p3"                    */
+  char name[48];           /* kernel family, e.g. "hex_div_vf_p3"                    */
   int64_t launches;
   double total_ms;         /* summed event-measured device time                      */
 } fr_kernel_time;

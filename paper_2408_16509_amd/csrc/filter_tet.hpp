@@ -187,9 +187,9 @@ __global__ void __launch_bounds__(TF_NT) tet_sown(const double* __restrict__ u, 
   sown[e] = ord_bits(smin);
 }
 
-// Detection: pessimistic test at every solution point, as the hexahedral detection.  With an RK stage source the pass also performs the stage
-// update (all E_pad elements), and cand64 (if not null) receives the FP64 stage state of
-// the flagged elements.
+// Detection: pessimistic test at every solution point, as the hexahedral detection.  With
+// an RK stage source the pass also performs the stage update (all E_pad elements), and
+// cand64 (if not null) receives the FP64 stage state of the flagged elements.
 template <typename Src>
 __global__ void __launch_bounds__(TF_NT) tet_filter_detect(Src src, const double* __restrict__ smin_a, int64_t E,
                                                            int64_t n, FiltPrm F, CandList L,

@@ -582,7 +582,12 @@ constexpr int64_t wide_blocks() {
 // values per point and element).  28^3 p = 4 FP64, us: 8 elements and 2 threads 223, 4 and 5
 // 251, 8 and 3 436 (over the registers of its 10 waves); 32^3 p = 3 FP64: 2 threads 147, 4 173,
 // 1 191; FP32 28^3 p = 4: 8 and 5 113, 8 and 2 141, 16 and 2 142; 32^3 p = 3: 16 elements and
-// 2 threads 73, 4 threads 75, 8 elements 78; 40^3 p = 2: 3 threads 76, 1 118.
+// 2 threads 73, 4 threads 75, 8 and 4 78; 40^3 p = 2: 3 threads 76, 1 118.  Whole right-hand
+// sides, us, here / half the elements / other threads: p = 1, 48^3 (1 thread) FP64 256 / 258 / 274,
+// FP32 94 / 99 / 99, curved 254 / 251 / 258 and 110 / 109 / 109; curved p = 2, 36^3 (1) 287 / 294 / 395
+// and 135 / 137 / 160; curved p = 3, 28^3 (4) 297 / 308 / 310 and 130 / 128 / 127; curved p = 4,
+// 8,400 elements (FP64 3, FP32 2) 270 / 279 / 301 and 102 / 105 / 122.  Half the elements would gain in
+// FP32 p = 3 straight (28^3 107 / 100) and 2-8 % on meshes of some hundred elements.
 template <typename T, int P>
 struct HexGradCfg {
   static constexpr int NE = P == 4 ? 8 : (sizeof(T) == 8 ? 1 : 2) * (P == 1 ? 32 : (P == 2 ? 16 : 8));

@@ -928,8 +928,8 @@ __global__ void __launch_bounds__(256) hex_face_ns(const T* __restrict__ uf, con
 // Navier--Stokes phase 2b: f = f_inv - f_v at the solution points and the
 // corrected divergence with the common fluxes of hex_face_ns at the line ends.
 // Each thread owns one column (i, j) of one element: it evaluates the transformed
-// flux of all three directions at its column's points once (every u and grad u
-// value is read once) into LDS, then gathers, for each of its points, the three
+// flux of all three directions at its column's points once (every state and viscous
+// flux value is read once) into LDS, then gathers, for each of its points, the three
 // line contractions through that point from LDS.
 template <typename T, bool DEV, int P, int NE, bool CUR = false>
 __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
@@ -948,7 +948,7 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns(
   const T gm1 = gamma - T(1);
   T* const rl = r + (int64_t)l * 5 * E + e;
   T iJ[N1], f3[N1][5];
-  // the state and gradient of the column's next point are loaded while the current
+  // the state and viscous flux of the column's next point are loaded while the current
   // point's fluxes are formed (two buffers), so a wave keeps loads in flight
   T ub[2][5], gb[2][9];
   const T *const ul = u + (int64_t)l * 5 * E + e, *const vl = vf + (int64_t)l * 9 * E + e;
@@ -1054,7 +1054,7 @@ __global__ void __launch_bounds__(NE*(P + 1)*(P + 1)) hex_div_ns_lds(
   const T gm1 = gamma - T(1);
   T* const rl = r + (int64_t)l * 5 * E + e;
   T iJ[N1];
-  // as in hex_div_ns: the next point's state and gradient load while the current
+  // as in hex_div_ns: the next point's state and viscous flux load while the current
   // point's fluxes are formed (this variant is held to 1-2 waves per SIMD by its LDS,
   // so registers are not what limits it)
   T ub[2][5], gb[2][9];

@@ -406,7 +406,6 @@ __global__ void __launch_bounds__(py_nt<T>()) pyr_div(const T* __restrict__ u, c
 // traces are in registers (5 values stored instead of 15), and stores S_i . f_v at the
 // solution points (12 instead of 15); the divergence reads both.  A two-sided switch takes
 // pyr_grad and pyr_div.
-// @PYRM@
 constexpr int PYM_NE = 16, PYM_NT = 256, PYM_KP = 56, PYM_M = 64, PYM_FT = 6, PYM_FM = 16 * PYM_FT, PYM_KL = 28 + 4 * 16;
 
 // Flux point of row `row` of flux tile ft (-1: padding), its face, its K row in the lift.
