@@ -681,8 +681,8 @@ __device__ __forceinline__ int gr_slot(int pt) {
 // global reads are issued first; the state goes to LDS, the line ends form u^ (own traces
 // stay in registers), each thread forms all 15 components of its points' gradients in
 // registers, and these replace the state in LDS for the traces: four barriers in all.
-// Bytes aside, its vector instructions (about 870 per FP32 point at p = 3) are what it pays:
-// addresses step from one base per array.  With the pass that follows it, against storing the
+// Bytes aside it pays for vector instructions (710 per FP32 point at p = 3, half of the issue slots;
+// addresses step from one base per array) and for its phases (waves wait half of their cycles).  With the pass that follows it, against storing the
 // 15 gradient components and their traces and forming both fluxes later, us (gradient / common
 // flux / divergence): 32^3 p = 3 FP32 76 / 49 / 83 -> 73 / 34 / 51, FP64 158 / 120 / 146 ->
 // 147 / 74 / 125; 28^3 p = 4 FP64 232 / 123 / 278 -> 223 / 80 / 242; 10^3 p = 3 FP64 gradient
