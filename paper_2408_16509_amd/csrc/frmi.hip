@@ -1421,12 +1421,12 @@ fr_status setup_impl(const fr_params* p, int64_t n_vert, const double* xyz, cons
     const bool is_tet = d.etype == FR_TET, is_hex = d.etype == FR_HEX, ns = p->system == FR_NAVIER_STOKES;
     const bool pair = side_mode_of(p->ldg_beta) != 0 &&
                       (!is_tet || tet_can_pair(tsz == sizeof(float), !hb.cmet.empty()));
-    const int rows_fp[3] = {is_tet ? 0 : 5, !ns || is_tet ? 0 : (is_hex ? 4 : (pair ? 0 : 15)), ns && (is_hex || pair) ? 5 : 0};
-    const int rows_sp = !ns ? 0 : (is_hex ? 9 : (pair ? 12 : 15));
-    void** const at_fp[3] = {&d.uf, &d.gradf, &d.fc};
-    for (int k = 0; k < 3; ++k)
-      if (rows_fp[k] && dalloc(c, (char**)at_fp[k], (size_t)d.nfp * rows_fp[k] * d.E * tsz)) return bail(FR_ERR_ALLOC);
-    if (rows_sp && dalloc(c, (char**)&d.grad, (size_t)d.nsp * rows_sp * d.E * tsz)) return bail(FR_ERR_ALLOC);
+    const int64_t rows[4] = {is_tet ? 0 : 5 * d.nfp, !ns ? 0 : d.nsp * (is_hex ? 9 : (pair ? 12 : 15)),
+                             !ns || is_tet ? 0 : d.nfp * (is_hex ? 4 : (pair ? 0 : 15)),
+                             ns && (is_hex || pair) ? 5 * d.nfp : 0};
+    void** const at[4] = {&d.uf, &d.grad, &d.gradf, &d.fc};
+    for (int k = 0; k < 4; ++k)
+      if (rows[k] && dalloc(c, (char**)at[k], (size_t)(rows[k] * d.E) * tsz)) return bail(FR_ERR_ALLOC);
     d.geo_t = d.geo;
     if (tsz == sizeof(float)) {
       std::vector<float> g32(hb.geo.begin(), hb.geo.end());
