@@ -335,10 +335,12 @@ fr_status layout_block(fr_ctx c, const DevBlock& b, const double* cin, double* c
     return FR_OK;
   }
   // chunks of 8 points (more, smaller blocks) or 40: 4,096 p = 4 hexahedra 9.7 / 12.1 and 9.2 / 9.7;
-  // 32,768 p = 3 29.1 / 33.5 and 26.1 / 28.9 (10.5 M values).  Past 16 M values, when both sides no longer
-  // fit the 256 MB last-level cache, unpacking takes the larger ones: 32,768 p = 4 81 / 97 and
-  // 79.5 / 64.8; 196,608 tetrahedra 146 / 154 and 148 / 125
-  const bool large = !PACK && values >= (int64_t)16 << 20;
+  // 32,768 p = 3 29.1 / 33.5 and 26.1 / 28.9 (10.5 M values).  Unpacking takes the larger ones past 16 M
+  // values, when both sides no longer fit the 256 MB last-level cache (32,768 p = 4 81 / 97 and 79.5 / 64.8;
+  // 196,608 tetrahedra 146 / 154 and 148 / 125), and past 3 M where one of them holds all points, so that an
+  // element's canonical values leave in one piece: 24,480 tetrahedra after a right-hand side 15.2 / 13.1,
+  // 18,432 12.0 / 10.7, 12,416 (2.2 M values) 8.7 / 9.4; 32,768 p = 2 14.3 / 12.9
+  const bool large = !PACK && values >= (int64_t)(b.nsp <= 40 ? 3 : 16) << 20;
 #define FR_LAYOUT(NSP)                                                                                          \
   case NSP:                                                                                                     \
     if (!large)                                                                                                 \
