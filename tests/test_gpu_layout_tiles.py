@@ -49,3 +49,12 @@ def test_either_side_of_the_tiles(kind, order, n):
 
 def test_larger_chunks():
     _round_trip(inputs.hex_box((30, 31, 29), permute_seed=3), 4, 8)      # 26,970 x 625: 16.9 M values
+
+
+@pytest.mark.parametrize("kind,order,n", [("tet", 4, (15, 13, 15)), ("tet", 4, (14, 14, 16)), ("hex", 2, (30, 31, 25)),
+                                          ("hex", 2, (29, 30, 27))])
+def test_chunks_of_all_points(kind, order, n):
+    """Either side of 3 M values (17,976 tetrahedra, 23,302 p = 2 hexahedra), where one chunk then holds
+    every point of an element."""
+    box = inputs.hex_box(n, permute_seed=3) if kind == "hex" else inputs.kuhn_split(inputs.hex_box(n), permute_seed=3)
+    _round_trip(box, order, 9)
